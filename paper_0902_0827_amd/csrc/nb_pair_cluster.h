@@ -176,8 +176,9 @@ __device__ __forceinline__ T group_sum(T v) {
 // apart, in their order: the matrix cores, otherwise idle, take the place of two of the three
 // exchange steps (a DPP step costs two moves and an addition in FP64).  No lane of another
 // candidate enters a sum, so that a value that is not finite stays with its own.
-// (FP64 pair kernel, 23.6k-atom box: 80.3 us before, 77.3 with these sums, the images chosen per
-// atom and the exclusion windows in LDS.)
+// (FP64 build + forces of the 23.6k-atom box: 107.4 us with the shares summed by DPP moves, an
+// image chosen for every pair and the exclusion masks in registers, the rest of the call as it
+// was; 101.2 with these sums, no image where none is needed and the windows in LDS.)
 __device__ __forceinline__ double rows_sum_f64(double v) {
   const double q = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
   return q + dpp_f64<kDppRowRor8>(q);
@@ -649,8 +650,12 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
     bool any_far = false;  // (set below, once the first candidates' loads are issued)
 
     uint4 ctr, half;  // the cluster's bounding box (below)
-    bool near = false;  // FP64: positions are taken as their images nearest the cluster's first atom
+    // FP64 half shell: the cluster's atoms lie together as given, and candidates within half of
+    // the box of its first atom, p0, as given, need no image (below).
+    bool near = false;
     double p0x = 0, p0y = 0, p0z = 0;
+    // ring position after the last staged candidate that does
+    uint32_t img_end = 0;
 
     // Per-lane sums for row ii's atom: force, energy (or dE/dq) and the per-type adjoint
     // sums in double for both paths (the mixed path adds each pair's single-precision
@@ -716,13 +721,18 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       nst = 0;
     };
 
+    // p lies within half of the box of p0 as given (false if either is not a number).
+    auto as_given = [&](const double4 &p) {
+      return (fabs(p.x - p0x) < 0.5 * bxx) & (fabs(p.y - p0y) < 0.5 * bxy) & (fabs(p.z - p0z) < 0.5 * bxz);
+    };
+
     // Evaluate pair (row ii's atom, ring entry head + jj) for navail <= J entries.
     // FAR and VIR: the cluster may have far exclusions, the virial may be wanted (both
     // then tested at run time).  The loops of several groups have a copy for each combination,
     // so that a pass of the common case is one basic block.
     // CHECK: test the half-shell stage's room for this group (false: the caller made room
     // for it beforehand, so that groups in a row form one basic block).
-    // NEAR (FP64): the images are already chosen.
+    // NEAR (FP64): every pair's displacement as given is its minimum image.
     auto process_group = [&](int navail, auto far_c, auto vir_c, auto check_c, auto near_c) {
       constexpr bool NEAR = decltype(near_c)::value;
       constexpr bool FAR = decltype(far_c)::value;
@@ -1003,12 +1013,16 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       }
       while (tail - head >= static_cast<uint32_t>(J)) process_group(J, far_c, vir_c, std::true_type{}, near_c);
     };
+    // (FP64 half shell) The ring's next group holds a candidate whose image is chosen pair by pair.
+    auto image_next = [&] { return !near || static_cast<int32_t>(img_end - head) > 0; };
     auto drain = [&](bool last) {
       using Yes = std::true_type;
       using No = std::false_type;
-      if constexpr (F64) {
-        if (HALF && near) drain_with(last, Yes{}, Yes{}, Yes{});
-        else drain_with(last, Yes{}, Yes{}, No{});
+      if constexpr (F64 && HALF) {
+        while (tail - head >= static_cast<uint32_t>(J) && image_next()) process_group(J, Yes{}, Yes{}, Yes{}, No{});
+        while (tail - head >= static_cast<uint32_t>(J)) process_group(J, Yes{}, Yes{}, Yes{}, Yes{});
+      } else if constexpr (F64) {
+        drain_with(last, Yes{}, Yes{}, No{});
       } else if constexpr (!PAIRS2 && !HALF) {
         drain_with(last, Yes{}, Yes{}, Yes{});
       } else if constexpr (MODE == kForces) {
@@ -1084,24 +1098,25 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       const uint32_t base3[3] = {u0.x, u0.y, u0.z};
       uint32_t cc[3], hh[3];
       if constexpr (F64 && HALF) {
-        // Images once per atom instead of once per pair (nine FP64 instructions of a group's
-        // 124): an atom within R of the cluster, at its image nearest the cluster's first atom,
-        // is nearest to every atom of the cluster there when R (as the box filter takes it) and
-        // the cluster together are shorter than half of the box.  Otherwise the images are
-        // chosen pair by pair.  (Not in the gradients: their FP64 error would grow.)
+        // No image (nine FP64 instructions of a group's 124) where none is needed: when the
+        // cluster's atoms lie within half of the box of its first atom as the caller gave them,
+        // and R (as the box filter takes it) and the cluster together are shorter than half of
+        // the box, then every pair with a candidate that lies within half of the box of that
+        // atom as given is nearest as given, and the image that a pair would choose is zero.
+        // Nothing is moved or rounded: the displacements are those of the pair-by-pair choice to
+        // the last bit, and an atom far away, or one that is not a number, affects its own pairs
+        // only.  (Up to a million boxes from the origin, where the fixed-point coordinates that
+        // the filter takes are exact enough.)
         near = true;
         for (int a = 0; a < 3; ++a) {
           const float ext = static_cast<float>(static_cast<uint32_t>(hi3[a]) - static_cast<uint32_t>(lo3[a]));
           const float reach = fmaf(ext, 1.0001f * static_cast<float>(sd->scale[a]), 1.0002f * c.rcf);
           near = near && reach < 0.4999f * static_cast<float>(sd->box[a]);
         }
+        p0x = first_lane_f64(pi64.x), p0y = first_lane_f64(pi64.y), p0z = first_lane_f64(pi64.z);
+        near = near && fabs(p0x) < 1e6 * bxx && fabs(p0y) < 1e6 * bxy && fabs(p0z) < 1e6 * bxz &&
+               __ballot(!as_given(pi64)) == 0;
         near = uni(static_cast<int>(near)) != 0;
-        if (near) {
-          p0x = first_lane_f64(pi64.x), p0y = first_lane_f64(pi64.y), p0z = first_lane_f64(pi64.z);
-          pi64.x -= bxx * rint((pi64.x - p0x) * ibx);
-          pi64.y -= bxy * rint((pi64.y - p0y) * iby);
-          pi64.z -= bxz * rint((pi64.z - p0z) * ibz);
-        }
       }
       for (int a = 0; a < 3; ++a) {
         // centre floor((lo + hi) / 2) and half-width max(hi - mid, mid - lo) = ceil(extent / 2),
@@ -1166,17 +1181,18 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       const int after = HALF ? (sj < first ? INT32_MAX : sj) : 0;
       const bool keep = valid && box_dist2(fj, ctr, half, s2x, s2y, s2z) < c.rc2_box;
       const uint64_t mk = __ballot(keep);
+      if constexpr (F64 && HALF) {
+        if (near) {  // wave-uniform
+          const uint64_t moved = __ballot(keep && !as_given(pj64));
+          if (moved) img_end = tail + static_cast<uint32_t>(__popcll(mk & (~0ull >> __clzll(static_cast<long long>(moved)))));
+        }
+      }
       const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mk >> 32),
                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u));
       const int slot = static_cast<int>((tail + below) & (kRing - 1));
       wave_lds_sync();  // earlier ring reads are complete before slots are reused
       if (keep) {
         if constexpr (F64) {
-          if (HALF && near) {  // wave-uniform
-            pj64.x -= bxx * rint((pj64.x - p0x) * ibx);
-            pj64.y -= bxy * rint((pj64.y - p0y) * iby);
-            pj64.z -= bxz * rint((pj64.z - p0z) * ibz);
-          }
           L.pos[slot] = pj64;
           L.meta[slot] = make_int4(static_cast<int>(fj.w), tj, HALF ? sj : 0, after);
         } else {
@@ -1207,7 +1223,7 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       using No = std::false_type;
       const int left = static_cast<int>(tail - head);
       if constexpr (F64) {
-        if (HALF && near) process_group(left, Yes{}, Yes{}, Yes{}, Yes{});
+        if (HALF && !image_next()) process_group(left, Yes{}, Yes{}, Yes{}, Yes{});
         else process_group(left, Yes{}, Yes{}, Yes{}, No{});
       } else {
         if (any_far) process_group(left, Yes{}, Yes{}, Yes{}, Yes{});
