@@ -160,7 +160,8 @@ typedef struct {
 
 /* Bytes of device workspace needed for this batch and these parameters.
  * Host only; no HIP call.  The same (system, params) must be passed to every
- * later call that uses the workspace. */
+ * later call that uses the workspace.  The size never falls as atoms are added or
+ * as boxes grow, so that a workspace sized for the largest batch serves all. */
 nb_status nb_workspace_bytes(const nb_system *sys, const nb_params *params, size_t *bytes /*[host]*/);
 
 /* Cell list (section 3): wraps each atom into its box, converts it to 32-bit
@@ -268,8 +269,9 @@ nb_status nb_pme_reciprocal(const nb_system *sys, const nb_params *params, const
  * taken from a scratch array of NB_NOALLOC_SCRATCH_BYTES (16 MiB) that the library holds
  * in device memory on every GPU it runs on, from the loading of the library's code until
  * the process ends.  The caller still passes the outputs.  No hipMalloc, hipFree or
- * other allocating call is made.  Batches whose workspace (nb_workspace_bytes) exceeds
- * NB_NOALLOC_SCRATCH_BYTES are refused with NB_ERR_CAPACITY before any work is enqueued
+ * other allocating call is made.  Batches whose workspace (nb_workspace_bytes, less its
+ * room for gradients) exceeds NB_NOALLOC_SCRATCH_BYTES are refused with NB_ERR_CAPACITY
+ * before any work is enqueued
  * (about 72,000 atoms at the densities of the configurations here).  The first call on a
  * device looks up that device's copy of the array (hipGetSymbolAddress).  Every call on
  * a GPU uses the same array, which keeps the last call's contents (the build rewrites

@@ -42,21 +42,30 @@ void set_error(const std::string &msg) { g_last_error = msg; }
 // The adjoint and the force VJP of small systems: a cluster's candidates are cut into parts, a
 // wave each, because one wave per cluster leaves SIMDs idle (below 1,024 clusters) or short of
 // waves to hide its latency.  As many parts as keep every wave resident (about 4,000 waves;
-// 3,000 for the FP64 force VJP, whose LDS is larger), at most 4 (each has its own sums in the
-// workspace, which eight would more than double for a small system); on the FP64 path three up to
+// 3,000 for the FP64 force VJP, whose LDS is larger), at most kMaxParts (each has its own sums in
+// the workspace, which eight would more than double for a small system); on the FP64 path three up to
 // 4,096 clusters, whose long waves then end more evenly.  Measured, call time with 1 part
 // against this rule (us): mixed adjoint 648 atoms 26 -> 16, 7.6k 37 -> 28, 13.7k 46 -> 42 and
 // 23.6k 60 -> 63 with 2 (kept whole); FP64 adjoint 50 -> 24, 70 -> 45, 90 -> 72, 116 -> 104;
 // FP64 force VJP 58 -> 27, 81 -> 59, 105 -> 95, 159 -> 142, and 48.6k atoms 243 -> 252 with 3
 // (kept whole).  (Forces and energies stay whole: the same system gives the same bits alone
 // and in a batch of any size.)
+constexpr int kMaxParts = 4;
+constexpr int64_t kPartsClusters = 4096;  // the most clusters that are cut, into three
 int grad_parts_for(const Plan &p, int mode) {
   if (p.cluster_size != 8 || p.n_clusters_max <= 0) return 1;
   const bool f64 = p.precision == NB_FP64;
   const int64_t n = p.n_clusters_max, waves = f64 && mode == kVJP ? 3000 : 4000;
-  if (f64 && n > 1500 && n <= 4096) return 3;
-  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(4, waves / n)));
+  if (f64 && n > 1500 && n <= kPartsClusters) return 3;
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(kMaxParts, waves / n)));
 }
+
+// Room for those parts' sums, for n clusters (or 8 n atoms, the most that n clusters hold): at
+// least n times the parts of every mode and precision, and never less for more, so that a
+// workspace sized for a batch serves every smaller one.  (It depends on neither the precision
+// nor the options that turn the parts off, so that the order of two batches' or two options'
+// sizes is that of their other arrays.)
+int64_t parts_room(int64_t n) { return std::min<int64_t>(kMaxParts * n, 3 * kPartsClusters); }
 
 int pair_parts(const Plan &p, int mode) {
   return mode == kAdjoint || mode == kVJP ? std::min(p.grad_parts, grad_parts_for(p, mode)) : 1;
@@ -142,7 +151,7 @@ nb_status make_plan(const nb_system *sys, const nb_params *prm, Plan *plan, bool
     return fail(NB_ERR_ARG, "the tables are not combined with the switch, 1-4 pairs or the per-atom kernel");
   p.table_n = p.table == 0 ? 0 : (prm->table_size ? prm->table_size : (p.table == 1 ? 4096 : 1024));
   p.desc.resize(B);
-  int64_t cells = 0, blocks = 0, clusters = 0, columns = 0;
+  int64_t cells = 0, blocks = 0, clusters = 0, columns = 0, clusters8 = 0;
   for (int b = 0; b < B; ++b) {
     SysDesc &d = p.desc[b];
     std::memset(&d, 0, sizeof(d));
@@ -174,6 +183,7 @@ nb_status make_plan(const nb_system *sys, const nb_params *prm, Plan *plan, bool
     d.clu_begin = static_cast<int32_t>(clusters);
     clusters += (nb + p.cluster_size - 1) / p.cluster_size + ncol;  // every column may end in a partial one
     d.clu_end = static_cast<int32_t>(clusters);
+    clusters8 += (nb + 7) / 8 + ncol;
     columns += ncol;
     cells += ncell;
     blocks += (nb + kBlock - 1) / kBlock;
@@ -209,7 +219,6 @@ nb_status make_plan(const nb_system *sys, const nb_params *prm, Plan *plan, bool
   l.atom_slot = take(4 * static_cast<size_t>(N));
   l.atom_fix = take(16 * static_cast<size_t>(N));
   l.tmp = take(4 * static_cast<size_t>(N));
-  l.s_range = cells + 1 <= kFuseCells ? take(8 * static_cast<size_t>(N)) : 0;
   l.s_fix = take(16 * static_cast<size_t>(N));
   l.s_pos64 = take(32 * static_cast<size_t>(N));
   l.s_q32 = take(4 * static_cast<size_t>(N));
@@ -218,22 +227,26 @@ nb_status make_plan(const nb_system *sys, const nb_params *prm, Plan *plan, bool
   l.excl_far = take(4 * static_cast<size_t>(N));
   const int64_t cluster_waves = (clusters * p.split + 7) / 8 * 8;
   const size_t nparts = static_cast<size_t>(std::max<int64_t>(std::max<int64_t>(blocks, cluster_waves), 1));
-  p.n_slots = static_cast<int64_t>(std::max(nparts, static_cast<size_t>(clusters * p.split * p.grad_parts)));
+  p.n_slots = static_cast<int64_t>(nparts);
   l.partials = take(8 * kPart * static_cast<size_t>(p.n_slots));
   l.adj_partials = take(8 * 2 * static_cast<size_t>(p.T) * static_cast<size_t>(p.n_slots));
   l.col_clu_start = take(4 * static_cast<size_t>(columns + 1));
-  l.part = take(32 * static_cast<size_t>(N) * static_cast<size_t>(p.split * p.grad_parts));
+  l.part = take(32 * static_cast<size_t>(N) * static_cast<size_t>(p.split));
   l.queue = take(4 * static_cast<size_t>(kXcds * kQueueStride));
   // half-shell accumulators: 4 components of one 64-bit limb (mixed) or two (FP64)
   l.jacc = p.kernel == NB_KERNEL_CLUSTER_HALF ? take((p.precision == NB_FP64 ? 64 : 32) * static_cast<size_t>(N)) : 0;
   l.p14_mask = p.has14 ? take(16 * static_cast<size_t>(N)) : 0;
   l.rtab = p.table ? take(16 * static_cast<size_t>(p.table_n + 1) * static_cast<size_t>(p.table)) : 0;
   l.vsort = take(32 * static_cast<size_t>(N));
+  l.s_range = l.vsort;  // (8 bytes per atom, read by the build's last launch; vsort lives within a force VJP)
   // one record per launch slot of the cluster kernels' static grid (at least one round of 8)
   p.n_item_slots = std::max<int64_t>(cluster_waves, kXcds);
   l.items = take(sizeof(ItemRec) * static_cast<size_t>(p.n_item_slots));
   l.col_info = take(16 * static_cast<size_t>(columns));
   l.atom_col = take(4 * static_cast<size_t>(N));
+  // the parts of small systems' gradients, after everything that the other calls use
+  l.grad_part = gradients ? take(8 * 32 * static_cast<size_t>(parts_room((N + 7) / 8))) : 0;
+  l.grad_adj = gradients ? take(8 * 2 * static_cast<size_t>(p.T) * static_cast<size_t>(parts_room(clusters8))) : 0;
   l.total = o;
   *plan = std::move(p);
   return NB_OK;
@@ -285,6 +298,17 @@ Dev dev_view(const Plan &p, void *ws) {
   d.jacc_fix = half ? reinterpret_cast<long long *>(base + l.jacc) : nullptr;
   d.jacc_lo = half && p.precision == NB_FP64 ? d.jacc_fix + 4 * p.N : nullptr;
   return d;
+}
+
+Dev parts_view(const Plan &p, const Dev &d, int mode) {
+  const int parts = pair_parts(p, mode);
+  if (parts == 1) return d;
+  char *base = reinterpret_cast<char *>(d.status) - p.lay.status;
+  Dev v = d;
+  v.part = reinterpret_cast<double4 *>(base + p.lay.grad_part);
+  v.adj_partials = reinterpret_cast<double *>(base + p.lay.grad_adj);
+  v.n_slots = p.n_clusters_max * parts;
+  return v;
 }
 
 }  // namespace nb

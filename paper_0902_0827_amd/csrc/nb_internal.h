@@ -98,6 +98,7 @@ struct Layout {
   size_t status, desc, tab64, tab32, cell_count, cell_start, atom_cell, atom_slot, atom_fix, tmp, s_range, scan_tiles;
   size_t s_fix, s_pos64, s_q32, s_type, excl_mask, excl_far, partials, adj_partials;
   size_t col_clu_start, part, queue, jacc, p14_mask, rtab, vsort, items, col_info, atom_col;
+  size_t grad_part, grad_adj;  // gradients in parts: as part and adj_partials, for every part
   size_t total;
 };
 
@@ -111,7 +112,7 @@ struct Plan {
   int div_xy = 2, div_z = 2;
   int split = 1;         // work items per cluster (cluster kernel)
   int cluster_size = 8;  // atoms per cluster (cluster kernel): 4 or 8
-  int grad_parts = 1;    // parts that a gradient launch may cut an item into (workspace room)
+  int grad_parts = 1;    // parts that a gradient launch may cut an item into
   int schedule = 2;      // NB_SCHED_STATIC or NB_SCHED_DYNAMIC (cluster kernel)
   int wg_per_cu = 16;    // resident one-wave workgroups per compute unit (dynamic schedule)
   double cutoff = 0, beta = 0, ke = 0;
@@ -122,7 +123,7 @@ struct Plan {
   // Tabulated variant: 0 direct, 1 linear, 2 cubic Hermite radial tables of table_n intervals.
   int table = 0, table_n = 0;
   int64_t n_cells = 0, n_blocks = 0, n_clusters_max = 0, n_columns = 0;
-  int64_t n_slots = 0;       // partial-sum slots: per-atom blocks, or parts of work items
+  int64_t n_slots = 0;       // partial-sum slots: per-atom blocks, or work items
   int64_t n_item_slots = 0;  // cluster kernels: launch slots (work items, upper bound, a multiple of 8)
   std::vector<SysDesc> desc;
   Layout lay{};
@@ -218,9 +219,12 @@ inline uint32_t cluster_key(const Plan &p) {
 // Parts that a launch of this mode cuts each item into (nb_api.cpp).
 int pair_parts(const Plan &p, int mode);
 
-// Host helpers (nb_api.cpp).  gradients = false: no room for the parts of gradient launches.
+// Host helpers (nb_api.cpp).  gradients = false: no room for the parts of gradient launches (a
+// workspace that none will use).
 nb_status make_plan(const nb_system *sys, const nb_params *prm, Plan *plan, bool gradients = true);
 Dev dev_view(const Plan &plan, void *ws);
+// The view of a launch of this mode: with parts, their own sums.
+Dev parts_view(const Plan &plan, const Dev &d, int mode);
 void set_error(const std::string &msg);
 
 // Optional events around pair-kernel launches (nb_pair_timer_start / _stop).

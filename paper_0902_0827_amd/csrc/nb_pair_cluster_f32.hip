@@ -10,8 +10,9 @@ void launch_cluster_grad_f32(const Plan &p, const Dev &d, const Consts &c, const
 void launch_cluster_grad_f64(const Plan &p, const Dev &d, const Consts &c, const Out &o, int mode, bool half,
                              hipStream_t s);
 
-void launch_cluster_pair(const Plan &p, const Dev &d, const Consts &c, const Out &o, int mode, hipStream_t s,
+void launch_cluster_pair(const Plan &p, const Dev &whole, const Consts &c, const Out &o, int mode, hipStream_t s,
                          double *energy, double *virial, const double *eps, double *grad_sigma, double *grad_eps) {
+  const Dev d = parts_view(p, whole, mode);
   // the adjoint and the force VJP stay full-shell
   const bool half = p.kernel == NB_KERNEL_CLUSTER_HALF && mode != kAdjoint && mode != kVJP;
   const bool f64 = p.precision == NB_FP64;
