@@ -245,8 +245,8 @@ nb_status nb_ewald_corrections(const nb_system *sys, const nb_params *params, vo
  * W_ab = -dE/d(strain_ab), row-major, or NULL].  FP64 arithmetic (either input
  * precision); ewald_beta > 0 and coulomb_k come from params, which is validated as for
  * the other calls.  `workspace` is its own buffer (not the nonbonded workspace) of
- * nb_pme_workspace_bytes bytes, 256-byte aligned, owned by the caller; it needs no
- * build.  It holds the grids and the work area of the FFTs, so calls with different
+ * nb_pme_workspace_bytes bytes, 256-byte aligned, owned by the caller (the size depends
+ * on n_systems, the grid and the device alone); it needs no build.  It holds the grids and the work area of the FFTs, so calls with different
  * workspaces may run concurrently on different streams.  The LDS additions of the
  * charge spreading are FP64 atomics, so results may vary in the last bits from run to
  * run.  Grids whose sizes have no prime factor above 7 and whose planes fit in LDS (up to

@@ -480,7 +480,7 @@ nb_status nb_pme_workspace_bytes(const nb_system *sys, const int32_t grid[3], si
     if (!sys || !bytes) return fail(NB_ERR_ARG, "null system or output pointer");
     if (sys->n_systems < 1) return fail(NB_ERR_ARG, "n_systems must be >= 1");
     nb::PmeLayout lay;
-    std::string why = nb::pme_layout(sys, grid, &lay);
+    std::string why = nb::pme_layout(sys->n_systems, grid, &lay);
     if (!why.empty()) return fail(NB_ERR_ARG, why);
     why = nb::pme_attach_plans(&lay);
     if (!why.empty()) return fail(NB_ERR_HIP, "nb_pme_workspace_bytes: " + why);
@@ -498,7 +498,7 @@ nb_status nb_pme_reciprocal(const nb_system *sys, const nb_params *params, const
     if (st != NB_OK) return st;
     if (!(params->ewald_beta > 0.0)) return fail(NB_ERR_ARG, "the reciprocal sum needs ewald_beta > 0");
     nb::PmeLayout lay;
-    std::string why = nb::pme_layout(sys, grid, &lay);
+    std::string why = nb::pme_layout(sys->n_systems, grid, &lay);
     if (!why.empty()) return fail(NB_ERR_ARG, why);
     if (!force && p.N > 0) return fail(NB_ERR_ARG, "force must not be NULL");
     if (!workspace) return fail(NB_ERR_WORKSPACE, "workspace is NULL");

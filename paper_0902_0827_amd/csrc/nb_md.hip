@@ -690,7 +690,7 @@ nb_status md_plan(const nb_system *sys, const nb_params *prm, const nb_md_params
       *why = "a PME grid needs ewald_beta > 0";
       return NB_ERR_ARG;
     }
-    std::string w = pme_layout(sys, md->pme_grid, &mp->pl);
+    std::string w = pme_layout(sys->n_systems, md->pme_grid, &mp->pl);
     if (!w.empty()) {
       *why = w;
       return NB_ERR_ARG;

@@ -21,13 +21,12 @@ struct PmeLayout {
   int64_t grid = 0, spec = 0, conv_blocks = 0;
   size_t real = 0, cplx = 0, partials = 0, work = 0, work_bytes = 0, total = 0;
   bool in_lds = false;  // transformed by this library's kernels, without FFT library plans
-  size_t bins = 0;      // bytes of the binned atoms at the start of `real` (in_lds)
   size_t tables = 0;    // FFT tables (in_lds)
 };
 
 // Fills `lay` for this batch and grid, without the FFT work area (host only, no HIP
 // call); returns "" or the reason the grid is refused.
-std::string pme_layout(const nb_system *sys, const int32_t grid[3], PmeLayout *lay);
+std::string pme_layout(int B, const int32_t grid[3], PmeLayout *lay);
 
 // Makes (or finds) the FFT plans of this layout on the current device and adds their
 // work area to it; returns "" or the reason the FFT library refused them.

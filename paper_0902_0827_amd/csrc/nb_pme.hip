@@ -17,8 +17,8 @@
 // order on the caller's stream, every system of a batch in the same launches:
 //
 //   k_pme_bin      per 1024 atoms: their scaled coordinates and charges, sorted by the
-//                  x-plane they start in (a counting sort in LDS); three more workgroups
-//                  write the tables of the FFTs;
+//                  x-plane they start in (a counting sort in LDS; left out where the grid is
+//                  too coarse to hold them); three more workgroups write the tables of the FFTs;
 //   k_pme_rows_fwd one workgroup per (system, x, block of y rows): the rows' charges summed
 //                  in LDS from the atoms that touch them, then their real FFTs along z in
 //                  place, and the half spectra stored by z frequency;
@@ -368,6 +368,14 @@ struct RowsLds {
   }
 };
 
+template <typename T>
+__device__ inline PmeAtom pme_atom(const T *__restrict__ pos, const T *__restrict__ charge, int64_t i,
+                                   const PmeSys &ps) {
+  return {scaled_coord(static_cast<double>(pos[3 * i + 0]), ps.invL[0], ps.K[0]),
+          scaled_coord(static_cast<double>(pos[3 * i + 1]), ps.invL[1], ps.K[1]),
+          scaled_coord(static_cast<double>(pos[3 * i + 2]), ps.invL[2], ps.K[2]), static_cast<double>(charge[i])};
+}
+
 // Scaled coordinates and charges of 1,024 atoms, sorted by the plane of their first x point
 // (a counting sort in LDS; the order within a plane is arbitrary), and where each plane
 // begins: [K1 + 1] offsets within the 1,024.  The rows kernel then reads, for its plane,
@@ -406,11 +414,7 @@ __global__ void __launch_bounds__(kBinAtoms) k_pme_bin(const T *__restrict__ pos
   PmeAtom at{0, 0, 0, 0};
   int bin = 0;
   if (have) {
-    const int64_t i = pb.a0[sb] + first + t;
-    at.ux = scaled_coord(static_cast<double>(pos[3 * i + 0]), ps.invL[0], ps.K[0]);
-    at.uy = scaled_coord(static_cast<double>(pos[3 * i + 1]), ps.invL[1], ps.K[1]);
-    at.uz = scaled_coord(static_cast<double>(pos[3 * i + 2]), ps.invL[2], ps.K[2]);
-    at.q = static_cast<double>(charge[i]);
+    at = pme_atom(pos, charge, pb.a0[sb] + first + t, ps);
     double frac;
     grid_cell(at.ux, K, &bin, &frac);
   }
@@ -453,9 +457,11 @@ __device__ inline void rows_of(const PmeBatch<CAP> &pb, const PmeGrid &g, int *b
 // rate of the FP64 LDS additions (16 per atom and plane, about 1.2 cycles each on a CU,
 // whatever the lanes that share an instruction): several workgroups per plane where one
 // system would otherwise leave CUs idle.
-template <int CAP>
-__global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_fwd(const PmeAtom *__restrict__ atoms,
-                                                              const uint16_t *__restrict__ offs, PmeBatch<CAP> pb, PmeGrid g,
+// atoms, offs: the binned atoms and where each plane's begin in each 1,024, or (T != PmeAtom) the
+// caller's positions and charges.
+template <typename T, typename U, int CAP>
+__global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_fwd(const T *__restrict__ atoms, const U *__restrict__ offs,
+                                                              PmeBatch<CAP> pb, PmeGrid g,
                                                               double2 *__restrict__ specs) {
   extern __shared__ __align__(16) double plane[];
   int b, x, y0;
@@ -467,56 +473,72 @@ __global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_fwd(const PmeAtom *__r
   for (int k = t; k < g.pairs * g.zs; k += threads) p.buf[k] = make_double2(0.0, 0.0);
   p.tables(g);
   __syncthreads();
-  // Charges: plane x is touched by the atoms that start in x .. x + 3, one run (two where
-  // that wraps) of each 1,024.  Each lane reads one such run's ends, 64 at a time; the waves
-  // then take the runs' pieces of 64 atoms in turn (input sorted in space has most of a
-  // plane's atoms in a few of the runs).
-  const int hi = x + 4 < K1 ? x + 4 : K1, wrap = x + 4 > K1 ? x + 4 - K1 : 0;
-  for (int c0 = pb.bin0[b]; c0 < pb.bin0[b + 1]; c0 += 64) {
-    const int mine = c0 + lane;
-    int my_s0 = 0, my_n0 = 0, my_n = 0;
-    if (mine < pb.bin0[b + 1]) {
-      const uint16_t *o = offs + static_cast<int64_t>(mine) * (K1 + 1);
-      my_s0 = o[x];
-      my_n0 = o[hi] - my_s0;
-      my_n = my_n0 + (wrap ? o[wrap] : 0);
+  // One atom's charges in the workgroup's rows of plane x.
+  auto add = [&](const PmeAtom at) {
+    int bx, by, bz;
+    double fx, fy, fz, wx[4], wy[4], wz[4], d[4];
+    grid_cell(at.uy, K2, &by, &fy);
+    int r0 = by - y0;  // the atom's rows are by - i (mod K2), i in [0, 4)
+    if (r0 < 0) r0 += K2;
+    if (r0 >= rows + 3) return;
+    grid_cell(at.ux, K1, &bx, &fx);
+    grid_cell(at.uz, K3, &bz, &fz);
+    int a = bx - x;  // the atom's point base - a (mod K1) is x
+    if (a < 0) a += K1;
+    spline4(fx, wx, d);
+    spline4(fy, wy, d);
+    spline4(fz, wz, d);
+    const double qa = at.q * (a == 0 ? wx[0] : a == 1 ? wx[1] : a == 2 ? wx[2] : wx[3]);
+    int iz[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) iz[j] = 2 * (bz - j < 0 ? bz - j + K3 : bz - j);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = r0 - i < 0 ? r0 - i + K2 : r0 - i;  // row within the workgroup's
+      if (r >= rows) continue;
+      double *row = plane + 2 * (r >> 1) * g.zs + (r & 1);
+      const double qy = qa * wy[i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) unsafeAtomicAdd(&row[iz[j]], qy * wz[j]);
     }
-    int pieces;
-    const int upto = wave_excl_scan_int((my_n + 63) >> 6, &pieces);
-    for (int piece = wave; piece < pieces; piece += waves) {
-      // the run holding this piece: the last one that begins at or before it
-      const int run = __popcll(__ballot(upto <= piece)) - 1;
-      const int s0 = __shfl(my_s0, run, 64), n0 = __shfl(my_n0, run, 64), n = __shfl(my_n, run, 64);
-      const int k = ((piece - __shfl(upto, run, 64)) << 6) + lane;
-      if (k >= n) continue;
-      const PmeAtom at =
-          atoms[pb.a0[b] + static_cast<int64_t>(c0 - pb.bin0[b] + run) * kBinAtoms + (k < n0 ? s0 + k : k - n0)];
-      int bx, by, bz;
-      double fx, fy, fz, wx[4], wy[4], wz[4], d[4];
-      grid_cell(at.uy, K2, &by, &fy);
-      int r0 = by - y0;  // the atom's rows are by - i (mod K2), i in [0, 4)
-      if (r0 < 0) r0 += K2;
-      if (r0 >= rows + 3) continue;
-      grid_cell(at.ux, K1, &bx, &fx);
-      grid_cell(at.uz, K3, &bz, &fz);
-      int a = bx - x;  // the atom's point base - a (mod K1) is x
-      if (a < 0) a += K1;
-      spline4(fx, wx, d);
-      spline4(fy, wy, d);
-      spline4(fz, wz, d);
-      const double qa = at.q * (a == 0 ? wx[0] : a == 1 ? wx[1] : a == 2 ? wx[2] : wx[3]);
-      int iz[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) iz[j] = 2 * (bz - j < 0 ? bz - j + K3 : bz - j);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = r0 - i < 0 ? r0 - i + K2 : r0 - i;  // row within the workgroup's
-        if (r >= rows) continue;
-        double *row = plane + 2 * (r >> 1) * g.zs + (r & 1);
-        const double qy = qa * wy[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) unsafeAtomicAdd(&row[iz[j]], qy * wz[j]);
+  };
+  if constexpr (std::is_same_v<T, PmeAtom>) {
+    // Charges: plane x is touched by the atoms that start in x .. x + 3, one run (two where
+    // that wraps) of each 1,024.  Each lane reads one such run's ends, 64 at a time; the waves
+    // then take the runs' pieces of 64 atoms in turn (input sorted in space has most of a
+    // plane's atoms in a few of the runs).
+    const int hi = x + 4 < K1 ? x + 4 : K1, wrap = x + 4 > K1 ? x + 4 - K1 : 0;
+    for (int c0 = pb.bin0[b]; c0 < pb.bin0[b + 1]; c0 += 64) {
+      const int mine = c0 + lane;
+      int my_s0 = 0, my_n0 = 0, my_n = 0;
+      if (mine < pb.bin0[b + 1]) {
+        const uint16_t *o = offs + static_cast<int64_t>(mine) * (K1 + 1);
+        my_s0 = o[x];
+        my_n0 = o[hi] - my_s0;
+        my_n = my_n0 + (wrap ? o[wrap] : 0);
       }
+      int pieces;
+      const int upto = wave_excl_scan_int((my_n + 63) >> 6, &pieces);
+      for (int piece = wave; piece < pieces; piece += waves) {
+        // the run holding this piece: the last one that begins at or before it
+        const int run = __popcll(__ballot(upto <= piece)) - 1;
+        const int s0 = __shfl(my_s0, run, 64), n0 = __shfl(my_n0, run, 64), n = __shfl(my_n, run, 64);
+        const int k = ((piece - __shfl(upto, run, 64)) << 6) + lane;
+        if (k >= n) continue;
+        const PmeAtom at =
+            atoms[pb.a0[b] + static_cast<int64_t>(c0 - pb.bin0[b] + run) * kBinAtoms + (k < n0 ? s0 + k : k - n0)];
+        add(at);
+      }
+    }
+  } else {
+    // every atom of the system, kept when it touches plane x
+    const PmeSys ps = make_sys(pb, b);
+    for (int i = t; i < pb.n[b]; i += threads) {
+      const PmeAtom at = pme_atom(atoms, offs, pb.a0[b] + i, ps);
+      int bx;
+      double fx;
+      grid_cell(at.ux, K1, &bx, &fx);
+      if ((bx < x ? bx - x + K1 : bx - x) < 4) add(at);
     }
   }
   __syncthreads();
@@ -833,8 +855,7 @@ int64_t bin_workgroups(const nb_system *sys, int b) {
 }
 }  // namespace
 
-std::string pme_layout(const nb_system *sys, const int32_t grid[3], PmeLayout *lay) {
-  const int B = sys->n_systems;
+std::string pme_layout(int B, const int32_t grid[3], PmeLayout *lay) {
   if (!grid) return "grid is NULL";
   for (int a = 0; a < 3; ++a)
     if (grid[a] < kMinGrid || grid[a] > kMaxGrid) return "grid sizes must be in [4, 1024]";
@@ -849,16 +870,8 @@ std::string pme_layout(const nb_system *sys, const int32_t grid[3], PmeLayout *l
   PmeGrid g;
   l.in_lds = pme_grid(l.K, B, &g);
   size_t off = 0, real_bytes = sizeof(double) * static_cast<size_t>(B) * l.grid;
-  if (l.in_lds) {
-    // the padded potential, in whose place the binned atoms wait until the planes are summed
-    real_bytes += sizeof(double) * kPhiPad * static_cast<size_t>(B) * grid[0] * grid[1];
-    if (sys->atom_offset) {
-      l.bins = align256(sizeof(PmeAtom) * static_cast<size_t>(std::max<int64_t>(sys->atom_offset[B], 0)));
-      size_t wgs = 0;
-      for (int b = 0; b < B; ++b) wgs += static_cast<size_t>(bin_workgroups(sys, b));
-      real_bytes = std::max(real_bytes, l.bins + sizeof(uint16_t) * wgs * (grid[0] + 1));
-    }
-  }
+  // (the padded potential, in whose place the binned atoms wait until the planes are summed)
+  if (l.in_lds) real_bytes += sizeof(double) * kPhiPad * static_cast<size_t>(B) * grid[0] * grid[1];
   l.real = off;
   off = align256(off + real_bytes);
   l.cplx = off;
@@ -888,7 +901,8 @@ std::string pme_attach_plans(PmeLayout *lay) {
 
 namespace {
 
-// The launch descriptor of systems [first, first + nsys).
+// The launch descriptor of systems [first, first + nsys).  bins: the binning workgroups of the
+// systems before them, to be carried on (null: the atoms are not binned).
 template <int CAP>
 PmeBatch<CAP> pme_chunk(const PmeLayout &lay, const nb_system *sys, double a, double ke, int first, int nsys,
                         int32_t *bins) {
@@ -910,11 +924,12 @@ PmeBatch<CAP> pme_chunk(const PmeLayout &lay, const nb_system *sys, double a, do
     pb.n[k] = static_cast<int32_t>(sys->atom_offset[b + 1] - sys->atom_offset[b]);
     pb.blk0[k] = blocks;
     blocks += static_cast<int32_t>((static_cast<int64_t>(pb.n[k]) * kGatherLanes + kBlock - 1) / kBlock);
+    if (!bins) continue;
     pb.bin0[k] = *bins;
     *bins += static_cast<int32_t>(bin_workgroups(sys, b));
   }
   pb.blk0[nsys] = blocks;
-  pb.bin0[nsys] = *bins;
+  if (bins) pb.bin0[nsys] = *bins;
   return pb;
 }
 
@@ -940,8 +955,16 @@ hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double bet
   PmeGrid g;
   if (!pme_grid(lay.K, lay.B, &g)) return hipErrorInvalidValue;
   double *phi = reinterpret_cast<double *>(base + lay.real);
+  // The atoms are binned where they fit into the potential's place (32 bytes each against 8 a
+  // grid point: grids of more than four points per atom, twice as coarse as one point per
+  // Angstrom, or finer).  Otherwise the rows kernel reads all of a system's atoms for each of its
+  // planes, so that the workspace depends on the number of systems and the grid alone.
+  const size_t atom_bytes = align256(sizeof(PmeAtom) * static_cast<size_t>(sys->atom_offset[lay.B]));
+  size_t bin_wgs = 0;
+  for (int b = 0; b < lay.B; ++b) bin_wgs += static_cast<size_t>(bin_workgroups(sys, b));
+  const bool binned = atom_bytes + sizeof(uint16_t) * bin_wgs * (lay.K[0] + 1) <= lay.cplx - lay.real;
   PmeAtom *atoms = reinterpret_cast<PmeAtom *>(base + lay.real);
-  uint16_t *offs = reinterpret_cast<uint16_t *>(base + lay.real + lay.bins);
+  uint16_t *offs = reinterpret_cast<uint16_t *>(base + lay.real + atom_bytes);
   double2 *spec = reinterpret_cast<double2 *>(base + lay.cplx);
   double *partials = reinterpret_cast<double *>(base + lay.partials);
   char *tab = base + lay.tables;
@@ -961,7 +984,7 @@ hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double bet
   auto each = [&](auto &&body) {
     int32_t bins = 0;
     for (int first = 0; first < lay.B; first += CAP)
-      body(pme_chunk<CAP>(lay, sys, a, ke, first, std::min(CAP, lay.B - first), &bins));
+      body(pme_chunk<CAP>(lay, sys, a, ke, first, std::min(CAP, lay.B - first), binned ? &bins : nullptr));
   };
   each([&](const PmeBatch<CAP> &pb) {
     const unsigned wgs = static_cast<unsigned>(pb.bin0[pb.nsys] - pb.bin0[0]) + (pb.first == 0 ? 3u : 0u);
@@ -974,8 +997,15 @@ hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double bet
                          static_cast<const float *>(sys->charge), pb, g, atoms, offs);
   });
   each([&](const PmeBatch<CAP> &pb) {
-    hipLaunchKernelGGL(k_pme_rows_fwd<CAP>, dim3(static_cast<unsigned>(lay.K[0] * g.blocks * pb.nsys)), rows_thr, rows_lds,
-                       s, atoms, offs, pb, g, spec);
+    const dim3 wgs(static_cast<unsigned>(lay.K[0] * g.blocks * pb.nsys));
+    auto rows = [&](const auto *from, const auto *beside) {
+      using T = std::remove_const_t<std::remove_reference_t<decltype(*from)>>;
+      using U = std::remove_const_t<std::remove_reference_t<decltype(*beside)>>;
+      hipLaunchKernelGGL((k_pme_rows_fwd<T, U, CAP>), wgs, rows_thr, rows_lds, s, from, beside, pb, g, spec);
+    };
+    if (binned) rows(atoms, offs);
+    else if (sys->pos_is_f64) rows(static_cast<const double *>(sys->pos), static_cast<const double *>(sys->charge));
+    else rows(static_cast<const float *>(sys->pos), static_cast<const float *>(sys->charge));
   });
   each([&](const PmeBatch<CAP> &pb) {
     hipLaunchKernelGGL(k_pme_slab<CAP>, dim3(static_cast<unsigned>(g.H * pb.nsys)), slab_thr, slab_lds, s, spec, pb, g,
@@ -1023,10 +1053,7 @@ hipError_t launch_pme(const PmeLayout &lay, const nb_system *sys, double beta, d
   const bool planes = plane_points <= kPlaneMaxPoints;
   const bool f64 = sys->pos_is_f64 != 0;
   const double a = kPi * kPi / (beta * beta);
-  auto chunk = [&](int first, int nsys) {
-    int32_t bins = 0;
-    return pme_chunk<kPmeChunk>(lay, sys, a, ke, first, nsys, &bins);
-  };
+  auto chunk = [&](int first, int nsys) { return pme_chunk<kPmeChunk>(lay, sys, a, ke, first, nsys, nullptr); };
   const dim3 blk(kBlock);
   // charge grids
   if (!planes)
