@@ -16,7 +16,7 @@ from __future__ import annotations
 import ctypes
 import os
 import struct
-from dataclasses import dataclass, field
+from dataclasses import dataclass
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -73,8 +73,8 @@ class nb_system(ctypes.Structure):
     ]
 
 
-# nb_system as a packed record: a call's view of a batch is formed by one struct.pack instead
-# of fourteen field assignments and two pointer casts (4.5 -> 2.5 us per call).
+# nb_system's layout: a call's view of a batch is formed by one struct.pack instead of fourteen
+# field assignments and two pointer casts (4.2 -> 2.4 us).
 _SYSTEM = struct.Struct("@iPPPiPPPPiPPPP")
 assert _SYSTEM.size == ctypes.sizeof(nb_system)
 
@@ -157,8 +157,7 @@ def load_library(path: str = LIB_PATH):
     if not os.path.exists(path):
         raise RuntimeError(f"{path} is missing: build it with `python -m paper_0902_0827_amd.build_lib`")
     lib = ctypes.CDLL(path)
-    # the system argument: a pointer to nb_system (ctypes.byref) or the packed record (bytes)
-    S, P, V = ctypes.c_void_p, ctypes.POINTER(nb_params), ctypes.c_void_p
+    S, P, V = ctypes.POINTER(nb_system), ctypes.POINTER(nb_params), ctypes.c_void_p
     sz = ctypes.c_size_t
     lib.nb_workspace_bytes.argtypes = [S, P, ctypes.POINTER(sz)]
     lib.nb_build_cells.argtypes = [S, P, V, sz, V]
@@ -234,7 +233,6 @@ class DeviceBatch:
     box: np.ndarray        # [B,3] float64
     pair14_offset: "object" = None  # [N+1] int32, or None
     pair14_index: "object" = None   # [n_14] int32 (at least one element), or None
-    _struct: nb_system = field(default=None, repr=False)
 
     @property
     def n_systems(self) -> int:
@@ -244,23 +242,20 @@ class DeviceBatch:
     def n_atoms(self) -> int:
         return int(self.atom_offset[-1])
 
-    def packed(self) -> bytes:
-        """The nb_system record of this batch, for one call; made anew on each call so that
-        tensor replacements are seen.  Its host arrays stay alive with the batch."""
+    def struct(self) -> nb_system:
+        """The nb_system view; made anew on each call so that tensor replacements are seen.  It
+        keeps the host arrays that it points to."""
         import torch
-        self._off_c = off = np.ascontiguousarray(self.atom_offset, np.int64)
-        self._box_c = box = np.ascontiguousarray(self.box, np.float64)
+        off = np.ascontiguousarray(self.atom_offset, np.int64)
+        box = np.ascontiguousarray(self.box, np.float64)
         at = lambda t: 0 if t is None else t.data_ptr()
-        return _SYSTEM.pack(
+        s = nb_system.from_buffer_copy(_SYSTEM.pack(
             off.shape[0] - 1, off.__array_interface__["data"][0], box.__array_interface__["data"][0], at(self.pos),
             1 if self.pos.dtype == torch.float64 else 0, at(self.charge), at(self.type), at(self.sigma), at(self.eps),
             self.sigma.shape[0], at(self.excl_offset), at(self.excl_index), at(self.pair14_offset),
-            at(self.pair14_index))
-
-    def struct(self) -> nb_system:
-        """The nb_system view; refreshed on each call so that tensor replacements are seen."""
-        self._struct = nb_system.from_buffer_copy(self.packed())
-        return self._struct
+            at(self.pair14_index)))
+        s._host = off, box
+        return s
 
 
 def device_batch(systems: Sequence, dtype=None, device: str = "cuda") -> DeviceBatch:
@@ -291,14 +286,14 @@ def device_batch(systems: Sequence, dtype=None, device: str = "cuda") -> DeviceB
 
 # --- the C ABI, one function each ------------------------------------------------------------
 
-def workspace_bytes(batch: DeviceBatch, params: nb_params, record: Optional[bytes] = None) -> int:
+def workspace_bytes(batch: DeviceBatch, params: nb_params, record: Optional[nb_system] = None) -> int:
     lib = load_library()
     n = ctypes.c_size_t()
-    _check(lib.nb_workspace_bytes(record or batch.packed(), ctypes.byref(params), ctypes.byref(n)))
+    _check(lib.nb_workspace_bytes(record or batch.struct(), ctypes.byref(params), ctypes.byref(n)))
     return int(n.value)
 
 
-def alloc_workspace(batch: DeviceBatch, params: nb_params, record: Optional[bytes] = None):
+def alloc_workspace(batch: DeviceBatch, params: nb_params, record: Optional[nb_system] = None):
     """A uint8 cuda tensor of the required size (torch allocations are 256-byte aligned)."""
     import torch
     ws = torch.empty(max(workspace_bytes(batch, params, record), 1), dtype=torch.uint8, device=batch.pos.device)
@@ -309,36 +304,36 @@ def alloc_workspace(batch: DeviceBatch, params: nb_params, record: Optional[byte
 def workspace_layout(batch: DeviceBatch, params: nb_params) -> nb_layout:
     lib = load_library()
     lay = nb_layout()
-    _check(lib.nb_workspace_layout(batch.packed(), ctypes.byref(params), ctypes.byref(lay)))
+    _check(lib.nb_workspace_layout(batch.struct(), ctypes.byref(params), ctypes.byref(lay)))
     return lay
 
 
-# record: the batch's packed() where the caller has just formed it (several calls in a row)
+# record: the batch's struct() where the caller has just formed it (several calls in a row)
 
-def build_cells(batch: DeviceBatch, params: nb_params, ws, stream=None, record: Optional[bytes] = None):
+def build_cells(batch: DeviceBatch, params: nb_params, ws, stream=None, record: Optional[nb_system] = None):
     lib = load_library()
-    _check(lib.nb_build_cells(record or batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_build_cells(record or batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                               _stream(stream)))
 
 
 def nonbonded_forces(batch: DeviceBatch, params: nb_params, ws, force, energy=None, virial=None, stream=None,
-                     record: Optional[bytes] = None):
+                     record: Optional[nb_system] = None):
     lib = load_library()
-    _check(lib.nb_nonbonded_forces(record or batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_nonbonded_forces(record or batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                                    _ptr(force), _ptr(energy), _ptr(virial), _stream(stream)))
 
 
 def nonbonded_forces_noalloc(batch: DeviceBatch, params: nb_params, force, energy=None, virial=None, stream=None):
     """Build + forces on the library's own scratch array (nb_nonbonded_forces_noalloc)."""
     lib = load_library()
-    _check(lib.nb_nonbonded_forces_noalloc(batch.packed(), ctypes.byref(params), _ptr(force),
+    _check(lib.nb_nonbonded_forces_noalloc(batch.struct(), ctypes.byref(params), _ptr(force),
                                            _ptr(energy), _ptr(virial), _stream(stream)))
 
 
 def ewald_corrections(batch: DeviceBatch, params: nb_params, ws, force, energy=None, virial=None, stream=None):
     """Excluded-pair and self corrections of the Ewald sum (nb_ewald_corrections)."""
     lib = load_library()
-    _check(lib.nb_ewald_corrections(batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_ewald_corrections(batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                                     _ptr(force), _ptr(energy), _ptr(virial), _stream(stream)))
 
 
@@ -351,7 +346,7 @@ def pme_workspace_bytes(batch: DeviceBatch, grid) -> int:
     lib = load_library()
     n = ctypes.c_size_t()
     gp, _keep = _grid(grid)
-    _check(lib.nb_pme_workspace_bytes(batch.packed(), gp, ctypes.byref(n)))
+    _check(lib.nb_pme_workspace_bytes(batch.struct(), gp, ctypes.byref(n)))
     return int(n.value)
 
 
@@ -367,21 +362,21 @@ def pme_reciprocal(batch: DeviceBatch, params: nb_params, grid, ws, force, energ
     """Reciprocal part of the Ewald sum by smooth PME on a K1 x K2 x K3 grid (nb_pme_reciprocal)."""
     lib = load_library()
     gp, _keep = _grid(grid)
-    _check(lib.nb_pme_reciprocal(batch.packed(), ctypes.byref(params), gp, _ptr(ws), ws.numel(),
+    _check(lib.nb_pme_reciprocal(batch.struct(), ctypes.byref(params), gp, _ptr(ws), ws.numel(),
                                  _ptr(force), _ptr(energy), _ptr(virial), _stream(stream)))
 
 
 def nonbonded_energy(batch: DeviceBatch, params: nb_params, ws, energy, atom_energy=None, stream=None,
-                     record: Optional[bytes] = None):
+                     record: Optional[nb_system] = None):
     lib = load_library()
-    _check(lib.nb_nonbonded_energy(record or batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_nonbonded_energy(record or batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                                    _ptr(energy), _ptr(atom_energy), _stream(stream)))
 
 
 def nonbonded_backward(batch: DeviceBatch, params: nb_params, ws, grad_energy, grad_pos=None,
                        grad_charge=None, grad_sigma=None, grad_eps=None, stream=None):
     lib = load_library()
-    _check(lib.nb_nonbonded_backward(batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_nonbonded_backward(batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                                      _ptr(grad_energy), _ptr(grad_pos), _ptr(grad_charge), _ptr(grad_sigma),
                                      _ptr(grad_eps), _stream(stream)))
 
@@ -390,7 +385,7 @@ def nonbonded_force_vjp(batch: DeviceBatch, params: nb_params, ws, v, grad_charg
                         grad_eps=None, stream=None):
     """dL/dq [N], dL/dsigma [T], dL/deps [T] of L = sum_i v_i . F_i (any output may be None)."""
     lib = load_library()
-    _check(lib.nb_nonbonded_force_vjp(batch.packed(), ctypes.byref(params), _ptr(ws), ws.numel(),
+    _check(lib.nb_nonbonded_force_vjp(batch.struct(), ctypes.byref(params), _ptr(ws), ws.numel(),
                                       _ptr(v), _ptr(grad_charge), _ptr(grad_sigma), _ptr(grad_eps),
                                       _stream(stream)))
 
@@ -454,7 +449,7 @@ def make_md_params(dt: float, temperature: float = 300.0, gamma: float = 1.0, se
 
 def md_workspace_bytes(batch: DeviceBatch, params: nb_params, md: nb_md_params) -> int:
     n = ctypes.c_size_t()
-    _check(load_library().nb_md_workspace_bytes(batch.packed(), ctypes.byref(params),
+    _check(load_library().nb_md_workspace_bytes(batch.struct(), ctypes.byref(params),
                                                 ctypes.byref(md), ctypes.byref(n)))
     return int(n.value)
 
@@ -468,7 +463,7 @@ def alloc_md_workspace(batch: DeviceBatch, params: nb_params, md: nb_md_params):
 
 def md_forces(batch: DeviceBatch, params: nb_params, topo: DeviceTopology, md: nb_md_params, ws, force,
               energy=None, stream=None):
-    _check(load_library().nb_md_forces(batch.packed(), ctypes.byref(params),
+    _check(load_library().nb_md_forces(batch.struct(), ctypes.byref(params),
                                        ctypes.byref(topo.struct()), ctypes.byref(md), _ptr(ws), ws.numel(),
                                        _ptr(force), _ptr(energy), _stream(stream)))
 
@@ -476,7 +471,7 @@ def md_forces(batch: DeviceBatch, params: nb_params, topo: DeviceTopology, md: n
 def md_run(batch: DeviceBatch, params: nb_params, topo: DeviceTopology, md: nb_md_params, ws, vel,
            first_step: int, n_steps: int, energy=None, stream=None):
     """n_steps integrator steps in place on batch.pos (float64) and vel."""
-    _check(load_library().nb_md_run(batch.packed(), ctypes.byref(params),
+    _check(load_library().nb_md_run(batch.struct(), ctypes.byref(params),
                                     ctypes.byref(topo.struct()), ctypes.byref(md), _ptr(ws), ws.numel(),
                                     _ptr(batch.pos), _ptr(vel), int(first_step), int(n_steps), _ptr(energy),
                                     _stream(stream)))
@@ -541,7 +536,7 @@ def _autograd():
         @staticmethod
         def forward(ctx, pos, charge, sigma, eps, batch: DeviceBatch, params: nb_params):
             b = _rebatch(batch, pos, charge, sigma, eps)
-            rec = b.packed()
+            rec = b.struct()
             ws = alloc_workspace(b, params, rec)
             build_cells(b, params, ws, record=rec)
             energy = torch.empty(b.n_systems, dtype=torch.float64, device=pos.device)
@@ -573,7 +568,7 @@ def _autograd():
         @staticmethod
         def forward(ctx, pos, charge, sigma, eps, batch: DeviceBatch, params: nb_params):
             b = _rebatch(batch, pos, charge, sigma, eps)
-            rec = b.packed()
+            rec = b.struct()
             ws = alloc_workspace(b, params, rec)
             build_cells(b, params, ws, record=rec)
             force = torch.empty((b.n_atoms, 3), dtype=torch.float64, device=pos.device)
