@@ -187,7 +187,7 @@ enum PairMode : int { kForces = 0, kEnergy = 1, kAdjoint = 2, kVJP = 3 };
 
 struct Consts {
   double rc2, beta, two_beta_sqrtpi, ke, sqrt_ke;
-  float rcf, rc2f, betaf, two_beta_sqrtpif, mb2l2e, rc2_box;
+  float rc2f, betaf, two_beta_sqrtpif, mb2l2e, rc2_box;
   int erfc_short;  // beta R within the short FP64 erfc table's range
   // FF variants: 1-4 scale factors and the LJ switch as x = (r^2 - sw_on2) sw_inv, S = 1 for
   // x <= 0 (no switch: sw_on2 = R^2 and sw_inv = 0, so S = 1 for every pair)

@@ -318,7 +318,6 @@ Consts make_consts(const Plan &p) {
   c.two_beta_sqrtpi = 2.0 * p.beta / 1.7724538509055160273;  // 2 beta / sqrt(pi)
   c.ke = p.ke;
   c.sqrt_ke = sqrt(p.ke);
-  c.rcf = static_cast<float>(p.cutoff);
   c.rc2f = static_cast<float>(c.rc2);
   c.betaf = static_cast<float>(p.beta);
   c.two_beta_sqrtpif = static_cast<float>(c.two_beta_sqrtpi);

@@ -23,8 +23,8 @@
 // cluster is one work item, and its wave writes the per-atom results in the caller's
 // atom order itself.  A cluster's candidates may instead be split over Q work items
 // (Q = 2..8; the gradients of small systems are split by their launch): each writes its part
-// of every atom's sums to its own slot, and k_finish adds the Q parts in a fixed order and converts them to the caller's atom order.
-// k_finish also reduces energies, virials and per-type sums.  Nothing is accumulated
+// of every atom's sums to its own slot, and k_finish adds the Q parts in a fixed order and
+// converts them to the caller's atom order.  k_finish also reduces energies, virials and per-type sums.  Nothing is accumulated
 // with atomics: results are deterministic.  The half-shell form (each pair once; the
 // mixed path's default for forces and energies) is described with the kernel: its
 // candidates' shares go to per-atom accumulators by atomics, in 64-bit fixed point on
@@ -53,8 +53,8 @@ constexpr int kRunPad = 4;           // sentinel entries after the last run
 // takes 134 and 3 waves fit.
 constexpr int kF64WavesPerEu = 4;
 // The FP64 half shell with 8-atom clusters has about three items per SIMD on the 23.6k-atom
-// box: held to 168 registers (3 waves per SIMD) it does not spill (77 us there; at 128 registers
-// it spills the prefetched candidates, which then wait for their loads: 91 us).
+// box: held to 168 registers (3 waves per SIMD) no form of it spills.  (Its general form takes
+// 153 to 155; the default one ends at 128, where four waves fit, without spilling either.)
 constexpr int kF64HalfWavesPerEu = 3;
 constexpr int kFinishBlock = 256;
 constexpr int kPairs2WavesPerCu = 16;  // 4 SIMDs x 4 resident waves of the two-group kernel
@@ -176,17 +176,11 @@ __device__ __forceinline__ T group_sum(T v) {
 // apart, in their order: the matrix cores, otherwise idle, take the place of two of the three
 // exchange steps (a DPP step costs two moves and an addition in FP64).  No lane of another
 // candidate enters a sum, so that a value that is not finite stays with its own.
-// (FP64 build + forces of the 23.6k-atom box: 107.4 us with the shares summed by DPP moves, an
-// image chosen for every pair and the exclusion masks in registers, the rest of the call as it
-// was; 101.2 with these sums, no image where none is needed and the windows in LDS.)
+// (FP64 build + forces, against DPP moves: 7.6k atoms 71.0 -> 68.5 us, 23.6k with the LJ switch
+// 111.0 -> 107.8, a batch of 293k atoms 722 -> 720.)
 __device__ __forceinline__ double rows_sum_f64(double v) {
   const double q = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
   return q + dpp_f64<kDppRowRor8>(q);
-}
-
-// Lane 0's value, in scalar registers.
-__device__ __forceinline__ double first_lane_f64(double v) {
-  return __hiloint2double(uni(__double2hiint(v)), uni(__double2loint(v)));
 }
 
 // 64-bit fixed point of the mixed-path half-shell accumulators: v * 2^32 rounded to the
@@ -276,7 +270,7 @@ struct WaveLds<true, false> {
 };
 
 template <>
-struct WaveLds<true, true> {  // FP64 half shell and FF variants
+struct WaveLds<true, true> {  // FP64: FF variants, the general form of the half shell's forces
   double4 pos[kRing];
   int4 meta[kRing];
   int2 runs[kMaxRuns + kRunPad];
@@ -391,9 +385,9 @@ constexpr int kVarCub = 3;    // radial terms from cubic Hermite tables (mixed f
 // loop, the queues or the division of the candidates is compiled in, which also spares the
 // scalar registers that would hold it (35 of them went to lanes of a vector register) and
 // leaves 93 vector registers instead of 127 to the mixed path's two-group form (101 to its
-// passes of four), 123 instead of 141 to the FP64 half shell as it was.  With the shorter fixed-point conversion below, build +
-// forces: 23.6k atoms 66.8 -> 64.4 us, 648 atoms 48.7 -> 46.8, 24 systems (293k atoms)
-// 400 -> 395, a million atoms 2,244 -> 2,215.
+// passes of four), 128 instead of 153 to the FP64 half shell.  With the shorter fixed-point
+// conversion below, build + forces when it was made: 23.6k atoms 66.8 -> 64.4 us, 648 atoms
+// 48.7 -> 46.8, 24 systems (293k atoms) 400 -> 395, a million atoms 2,244 -> 2,215.
 // GEN = true: Q0 items per cluster as the build recorded them, each cut into `sub` parts by
 // the launch (blockIdx.y), static or dynamic.
 template <bool F64, int MODE, bool TABLDS, int K, bool HALF, bool PAIRS2, int VAR, bool GEN>
@@ -415,9 +409,12 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
   // force VJP: each staged candidate's v_j (sorted copy), beside the ring
   __shared__ std::conditional_t<MODE == kVJP, std::conditional_t<F64, double4, float4>, int> VJ[MODE == kVJP ? kRing : 1];
   static_assert(TAB == 0 || (!F64 && MODE != kAdjoint), "tables: mixed forces and energies only");
-  // The windows in LDS cost eight instructions less per group than the masks in registers; the
-  // FP64 gradients, whose LDS limits the resident waves, keep the masks.
-  constexpr bool EXW = !F64 || FF || HALF;
+  // The windows in LDS cost eight instructions less per group than the masks in registers, and a
+  // kilobyte.  The FP64 path, where LDS limits the resident waves, keeps the masks, but for the
+  // form with several items or a schedule (GEN), whose registers are short: forces of 648 atoms
+  // in two items per cluster 38.5 us with masks, 36.9 with windows, 23.6k 101.2 and 97.6; the
+  // default form's 56.7 and 57.9, 85.1 and 89.2; energies of a batch of 293k atoms 401 and 417.
+  constexpr bool EXW = !F64 || FF || (HALF && K == 8 && GEN && MODE == kForces);
   __shared__ WaveLds<F64, EXW> L;
   TypePairLds<F64, MODE> *const TL = reinterpret_cast<TypePairLds<F64, MODE> *>(tab_lds);
   const int lane = static_cast<int>(threadIdx.x);
@@ -650,12 +647,6 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
     bool any_far = false;  // (set below, once the first candidates' loads are issued)
 
     uint4 ctr, half;  // the cluster's bounding box (below)
-    // FP64 half shell: the cluster's atoms lie together as given, and candidates within half of
-    // the box of its first atom, p0, as given, need no image (below).
-    bool near = false;
-    double p0x = 0, p0y = 0, p0z = 0;
-    // ring position after the last staged candidate that does
-    uint32_t img_end = 0;
 
     // Per-lane sums for row ii's atom: force, energy (or dE/dq) and the per-type adjoint
     // sums in double for both paths (the mixed path adds each pair's single-precision
@@ -721,20 +712,13 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       nst = 0;
     };
 
-    // p lies within half of the box of p0 as given (false if either is not a number).
-    auto as_given = [&](const double4 &p) {
-      return (fabs(p.x - p0x) < 0.5 * bxx) & (fabs(p.y - p0y) < 0.5 * bxy) & (fabs(p.z - p0z) < 0.5 * bxz);
-    };
-
     // Evaluate pair (row ii's atom, ring entry head + jj) for navail <= J entries.
     // FAR and VIR: the cluster may have far exclusions, the virial may be wanted (both
     // then tested at run time).  The loops of several groups have a copy for each combination,
     // so that a pass of the common case is one basic block.
     // CHECK: test the half-shell stage's room for this group (false: the caller made room
     // for it beforehand, so that groups in a row form one basic block).
-    // NEAR (FP64): every pair's displacement as given is its minimum image.
-    auto process_group = [&](int navail, auto far_c, auto vir_c, auto check_c, auto near_c) {
-      constexpr bool NEAR = decltype(near_c)::value;
+    auto process_group = [&](int navail, auto far_c, auto vir_c, auto check_c) {
       constexpr bool FAR = decltype(far_c)::value;
       constexpr bool VIR = decltype(vir_c)::value;
       // head is a multiple of J (only an item's last group is partial) and J divides
@@ -798,11 +782,9 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
         dxd = pi64.x - pj64.x;
         dyd = pi64.y - pj64.y;
         dzd = pi64.z - pj64.z;
-        if constexpr (!NEAR) {
-          dxd -= bxx * rint(dxd * ibx);
-          dyd -= bxy * rint(dyd * iby);
-          dzd -= bxz * rint(dzd * ibz);
-        }
+        dxd -= bxx * rint(dxd * ibx);
+        dyd -= bxy * rint(dyd * iby);
+        dzd -= bxz * rint(dzd * ibz);
         r2d = dxd * dxd + dyd * dyd + dzd * dzd;
         hit = ivalid & jv & (r2d < c.rc2) & other;
       } else {
@@ -987,13 +969,13 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
     };
 
     // N groups in a row, as one basic block, so that their loads and latencies overlap.
-    auto groups = [&](auto n_c, auto far_c, auto vir_c, auto near_c) {
+    auto groups = [&](auto n_c, auto far_c, auto vir_c) {
       constexpr int N = decltype(n_c)::value;
       if constexpr (HALF) {
         if (nst + N * J > kStage<F64>) flush();  // room for all N groups' shares
       }
 #pragma unroll
-      for (int g = 0; g < N; ++g) process_group(J, far_c, vir_c, std::false_type{}, near_c);
+      for (int g = 0; g < N; ++g) process_group(J, far_c, vir_c, std::false_type{});
     };
     // Every complete group in the ring; with PAIRS2 two at a time while there are two.  The half
     // shell takes four at a time while there are four (one chunk brings about four), and until
@@ -1001,41 +983,34 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
     // four (23.6k-atom box 43.7 -> 42.9 us, 648 atoms 28.9 -> 28.5, 24 boxes 353 -> 350; the
     // full-shell adjoint 54.9 -> 56.2, so not there), but for clusters with far exclusions, whose
     // groups branch.  (The FP64 group would spill at twice its registers.)
-    auto drain_with = [&](bool last, auto far_c, auto vir_c, auto near_c) {
+    auto drain_with = [&](bool last, auto far_c, auto vir_c) {
       if constexpr (!F64 && PAIRS2) {
         if constexpr (HALF && !decltype(far_c)::value) {
           while (tail - head >= 4u * static_cast<uint32_t>(J))
-            groups(std::integral_constant<int, 4>{}, far_c, vir_c, near_c);
+            groups(std::integral_constant<int, 4>{}, far_c, vir_c);
           if (!last) return;
         }
         while (tail - head >= 2u * static_cast<uint32_t>(J))
-          groups(std::integral_constant<int, 2>{}, far_c, vir_c, near_c);
+          groups(std::integral_constant<int, 2>{}, far_c, vir_c);
       }
-      while (tail - head >= static_cast<uint32_t>(J)) process_group(J, far_c, vir_c, std::true_type{}, near_c);
+      while (tail - head >= static_cast<uint32_t>(J)) process_group(J, far_c, vir_c, std::true_type{});
     };
-    // (FP64 half shell) The ring's next group holds a candidate whose image is chosen pair by pair.
-    auto image_next = [&] { return !near || static_cast<int32_t>(img_end - head) > 0; };
     auto drain = [&](bool last) {
       using Yes = std::true_type;
       using No = std::false_type;
-      if constexpr (F64 && HALF) {
-        while (tail - head >= static_cast<uint32_t>(J) && image_next()) process_group(J, Yes{}, Yes{}, Yes{}, No{});
-        while (tail - head >= static_cast<uint32_t>(J)) process_group(J, Yes{}, Yes{}, Yes{}, Yes{});
-      } else if constexpr (F64) {
-        drain_with(last, Yes{}, Yes{}, No{});
-      } else if constexpr (!PAIRS2 && !HALF) {
-        drain_with(last, Yes{}, Yes{}, Yes{});
+      if constexpr (F64 || (!PAIRS2 && !HALF)) {
+        drain_with(last, Yes{}, Yes{});
       } else if constexpr (MODE == kForces) {
         if (any_far) {
-          if (o.want_virial) drain_with(last, Yes{}, Yes{}, Yes{});
-          else drain_with(last, Yes{}, No{}, Yes{});
+          if (o.want_virial) drain_with(last, Yes{}, Yes{});
+          else drain_with(last, Yes{}, No{});
         } else {
-          if (o.want_virial) drain_with(last, No{}, Yes{}, Yes{});
-          else drain_with(last, No{}, No{}, Yes{});
+          if (o.want_virial) drain_with(last, No{}, Yes{});
+          else drain_with(last, No{}, No{});
         }
       } else {
-        if (any_far) drain_with(last, Yes{}, No{}, Yes{});
-        else drain_with(last, No{}, No{}, Yes{});
+        if (any_far) drain_with(last, Yes{}, No{});
+        else drain_with(last, No{}, No{});
       }
     };
 
@@ -1097,27 +1072,6 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       const int lo3[3] = {lox, loy, loz}, hi3[3] = {hix, hiy, hiz};
       const uint32_t base3[3] = {u0.x, u0.y, u0.z};
       uint32_t cc[3], hh[3];
-      if constexpr (F64 && HALF) {
-        // No image (nine FP64 instructions of a group's 124) where none is needed: when the
-        // cluster's atoms lie within half of the box of its first atom as the caller gave them,
-        // and R (as the box filter takes it) and the cluster together are shorter than half of
-        // the box, then every pair with a candidate that lies within half of the box of that
-        // atom as given is nearest as given, and the image that a pair would choose is zero.
-        // Nothing is moved or rounded: the displacements are those of the pair-by-pair choice to
-        // the last bit, and an atom far away, or one that is not a number, affects its own pairs
-        // only.  (Up to a million boxes from the origin, where the fixed-point coordinates that
-        // the filter takes are exact enough.)
-        near = true;
-        for (int a = 0; a < 3; ++a) {
-          const float ext = static_cast<float>(static_cast<uint32_t>(hi3[a]) - static_cast<uint32_t>(lo3[a]));
-          const float reach = fmaf(ext, 1.0001f * static_cast<float>(sd->scale[a]), 1.0002f * c.rcf);
-          near = near && reach < 0.4999f * static_cast<float>(sd->box[a]);
-        }
-        p0x = first_lane_f64(pi64.x), p0y = first_lane_f64(pi64.y), p0z = first_lane_f64(pi64.z);
-        near = near && fabs(p0x) < 1e6 * bxx && fabs(p0y) < 1e6 * bxy && fabs(p0z) < 1e6 * bxz &&
-               __ballot(!as_given(pi64)) == 0;
-        near = uni(static_cast<int>(near)) != 0;
-      }
       for (int a = 0; a < 3; ++a) {
         // centre floor((lo + hi) / 2) and half-width max(hi - mid, mid - lo) = ceil(extent / 2),
         // from the extent hi - lo in 32 bits (it is below 2^32)
@@ -1181,12 +1135,6 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       const int after = HALF ? (sj < first ? INT32_MAX : sj) : 0;
       const bool keep = valid && box_dist2(fj, ctr, half, s2x, s2y, s2z) < c.rc2_box;
       const uint64_t mk = __ballot(keep);
-      if constexpr (F64 && HALF) {
-        if (near) {  // wave-uniform
-          const uint64_t moved = __ballot(keep && !as_given(pj64));
-          if (moved) img_end = tail + static_cast<uint32_t>(__popcll(mk & (~0ull >> __clzll(static_cast<long long>(moved)))));
-        }
-      }
       const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mk >> 32),
                                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mk), 0u));
       const int slot = static_cast<int>((tail + below) & (kRing - 1));
@@ -1223,11 +1171,10 @@ k_pair_cluster(Dev d, Consts c, Out o, int q_arg, int sub_arg, int dynamic_arg) 
       using No = std::false_type;
       const int left = static_cast<int>(tail - head);
       if constexpr (F64) {
-        if (HALF && !image_next()) process_group(left, Yes{}, Yes{}, Yes{}, Yes{});
-        else process_group(left, Yes{}, Yes{}, Yes{}, No{});
+        process_group(left, Yes{}, Yes{}, Yes{});
       } else {
-        if (any_far) process_group(left, Yes{}, Yes{}, Yes{}, Yes{});
-        else process_group(left, No{}, Yes{}, Yes{}, Yes{});
+        if (any_far) process_group(left, Yes{}, Yes{}, Yes{});
+        else process_group(left, No{}, Yes{}, Yes{});
       }
     }
     if (dynamic && !requested && !(closed & (1u << home))) {  // an item without candidates
