@@ -22,6 +22,7 @@ struct PmeLayout {
   size_t real = 0, cplx = 0, partials = 0, work = 0, work_bytes = 0, total = 0;
   bool in_lds = false;  // transformed by this library's kernels, without FFT library plans
   size_t tables = 0;    // FFT tables (in_lds)
+  size_t systems = 0;   // descriptors of a large batch's systems (in_lds)
 };
 
 // Fills `lay` for this batch and grid, without the FFT work area (host only, no HIP

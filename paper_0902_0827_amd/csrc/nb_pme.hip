@@ -47,6 +47,7 @@
 #include <mutex>
 #include <tuple>
 #include <type_traits>
+#include <vector>
 
 #include "nb_internal.h"
 #include "nb_pair_common.h"
@@ -93,9 +94,24 @@ struct PmeBatch {
   int32_t bin0[CAP + 1];    // first k_pme_bin workgroup of each system (whole batch)
 };
 
+// The same for a batch of more systems than travel in one launch's arguments, with the arrays in
+// the workspace, written by k_pme_bin_table: one launch per step for all of them instead of one
+// for each kPmeChunk, which took 7 us each (100 systems of 648 atoms on 20^3: 142 us with five
+// launches for each 32, 122 through hipFFT, 77 with the table).
+struct PmeTable {
+  int nsys;   // systems in this launch
+  int first;  // batch index of its first system
+  int K[3];
+  int wg0, wgs;  // gather workgroups of the systems before this launch's, and of its own
+  double a, ke;
+  double (*L)[3], (*invL)[3];
+  int64_t *a0;
+  int32_t *n, *blk0, *bin0;
+};
+
 // System k of the launch.
-template <int CAP>
-__host__ __device__ inline PmeSys make_sys(const PmeBatch<CAP> &pb, int k) {
+template <typename PB>
+__host__ __device__ inline PmeSys make_sys(const PB &pb, int k) {
   PmeSys ps;
   for (int d = 0; d < 3; ++d) {
     ps.L[d] = pb.L[k][d];
@@ -116,6 +132,26 @@ __device__ inline int system_of_wg(const PmeBatch<CAP> &pb, const int32_t (&firs
   const int lane = static_cast<int>(threadIdx.x) & 63;
   return __builtin_amdgcn_readfirstlane(__popcll(__ballot(lane < pb.nsys && first[lane < pb.nsys ? lane : 0] <= wg)) - 1);
 }
+// (a table: a 64-way search, two rounds for 4,096 systems)
+__device__ inline int system_of_wg(const PmeTable &pb, const int32_t *first, int wg) {
+  int lo = 0, hi = pb.nsys - 1;  // the answer is in [lo, hi]
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  while (hi > lo) {
+    const int step = (hi - lo + 64) >> 6, probe = lo + lane * step;
+    const uint64_t m = __ballot(probe <= hi && first[probe <= hi ? probe : lo] <= wg);  // (lane 0 always)
+    lo += (63 - __clzll(static_cast<long long>(m))) * step;
+    hi = lo + step - 1 < hi ? lo + step - 1 : hi;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Gather workgroups of a launch, and those of the batch's systems before it.
+template <int CAP>
+__device__ inline int gather_wgs(const PmeBatch<CAP> &pb) { return pb.blk0[pb.nsys]; }
+template <int CAP>
+__device__ inline int gather_wg0(const PmeBatch<CAP> &) { return 0; }
+__device__ inline int gather_wgs(const PmeTable &pb) { return pb.wgs; }
+__device__ inline int gather_wg0(const PmeTable &pb) { return pb.wg0; }
 
 inline size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
@@ -382,9 +418,8 @@ __device__ inline PmeAtom pme_atom(const T *__restrict__ pos, const T *__restric
 // one run of each 1,024 instead of testing every atom.  The last three workgroups of the
 // batch's first launch write the tables instead, one dimension each.
 template <typename T, int CAP>
-__global__ void __launch_bounds__(kBinAtoms) k_pme_bin(const T *__restrict__ pos, const T *__restrict__ charge,
-                                                       PmeBatch<CAP> pb, PmeGrid g, PmeAtom *__restrict__ atoms,
-                                                       uint16_t *__restrict__ offs) {
+__device__ inline void pme_bin(const T *__restrict__ pos, const T *__restrict__ charge, const PmeBatch<CAP> &pb,
+                               const PmeGrid &g, PmeAtom *__restrict__ atoms, uint16_t *__restrict__ offs) {
   __shared__ int cnt[kMaxGrid + 1];
   __shared__ int tot[kBinAtoms / 64];
   const int t = static_cast<int>(threadIdx.x), lane = t & 63, wave = t >> 6;
@@ -444,9 +479,41 @@ __global__ void __launch_bounds__(kBinAtoms) k_pme_bin(const T *__restrict__ pos
   if (have) atoms[pb.a0[sb] + first + cnt[bin] + slot] = at;
 }
 
+template <typename T, int CAP>
+__global__ void __launch_bounds__(kBinAtoms) k_pme_bin(const T *__restrict__ pos, const T *__restrict__ charge,
+                                                       PmeBatch<CAP> pb, PmeGrid g, PmeAtom *__restrict__ atoms,
+                                                       uint16_t *__restrict__ offs) {
+  pme_bin<T, CAP>(pos, charge, pb, g, atoms, offs);
+}
+
+// The same for a batch with a table: the last workgroup writes this launch's systems into it.
+template <typename T>
+__global__ void __launch_bounds__(kBinAtoms) k_pme_bin_table(const T *__restrict__ pos, const T *__restrict__ charge,
+                                                             PmeBatch<kPmeChunk> pb, PmeGrid g,
+                                                             PmeAtom *__restrict__ atoms, uint16_t *__restrict__ offs,
+                                                             PmeTable tab) {
+  if (blockIdx.x + 1 < gridDim.x) {
+    pme_bin<T, kPmeChunk>(pos, charge, pb, g, atoms, offs);
+    return;
+  }
+  const int k = static_cast<int>(threadIdx.x), at = pb.first + k;
+  if (k < pb.nsys) {
+    for (int d = 0; d < 3; ++d) {
+      tab.L[at][d] = pb.L[k][d];
+      tab.invL[at][d] = pb.invL[k][d];
+    }
+    tab.a0[at] = pb.a0[k];
+    tab.n[at] = pb.n[k];
+  }
+  if (k <= pb.nsys) {
+    tab.blk0[at] = pb.blk0[k];
+    tab.bin0[at] = pb.bin0[k];
+  }
+}
+
 // Workgroup -> (system of the launch, x-plane, first row).
-template <int CAP>
-__device__ inline void rows_of(const PmeBatch<CAP> &pb, const PmeGrid &g, int *b, int *x, int *y0) {
+template <typename PB>
+__device__ inline void rows_of(const PB &pb, const PmeGrid &g, int *b, int *x, int *y0) {
   const int wg = static_cast<int>(blockIdx.x), plane = wg / g.blocks;
   *y0 = (wg - plane * g.blocks) * 2 * g.pairs;
   *b = plane / pb.K[0];
@@ -459,9 +526,9 @@ __device__ inline void rows_of(const PmeBatch<CAP> &pb, const PmeGrid &g, int *b
 // system would otherwise leave CUs idle.
 // atoms, offs: the binned atoms and where each plane's begin in each 1,024, or (T != PmeAtom) the
 // caller's positions and charges.
-template <typename T, typename U, int CAP>
+template <typename T, typename U, typename PB>
 __global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_fwd(const T *__restrict__ atoms, const U *__restrict__ offs,
-                                                              PmeBatch<CAP> pb, PmeGrid g,
+                                                              PB pb, PmeGrid g,
                                                               double2 *__restrict__ specs) {
   extern __shared__ __align__(16) double plane[];
   int b, x, y0;
@@ -558,8 +625,8 @@ __global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_fwd(const T *__restric
 
 // The inverse of k_pme_rows_fwd: phi of the rows, each led by copies of its last kPhiPad
 // values.
-template <int CAP>
-__global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_inv(const double2 *__restrict__ specs, PmeBatch<CAP> pb, PmeGrid g,
+template <typename PB>
+__global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_inv(const double2 *__restrict__ specs, PB pb, PmeGrid g,
                                                               double *__restrict__ phis) {
   extern __shared__ __align__(16) double plane[];
   int b, x, y0;
@@ -604,8 +671,8 @@ __global__ void __launch_bounds__(kPlaneBlock) k_pme_rows_inv(const double2 *__r
 // traffic (23 accesses per radix-8 butterfly, 16 without twiddles) and FP64 arithmetic on
 // one CU.  C(m) is separable but for 1/m^2: exp(-pi^2 m^2/beta^2) and |b|^2 are products of
 // one factor per dimension, formed once per line.
-template <int CAP>
-__global__ void __launch_bounds__(kPlaneBlock) k_pme_slab(double2 *__restrict__ specs, PmeBatch<CAP> pb, PmeGrid g, int want,
+template <typename PB>
+__global__ void __launch_bounds__(kPlaneBlock) k_pme_slab(double2 *__restrict__ specs, PB pb, PmeGrid g, int want,
                                                           double *__restrict__ partials_all) {
   extern __shared__ __align__(16) double plane[];
   __shared__ double red[kPlaneBlock / 64][8];
@@ -686,14 +753,14 @@ __device__ inline double octet_sum(double v) {
 // Workgroups past the launch's atoms each reduce one system's partials.
 constexpr int kGatherLanes = 8;
 
-template <typename T, bool PADDED, int CAP>
+template <typename T, bool PADDED, typename PB>
 __global__ void __launch_bounds__(kBlock) k_pme_gather(const T *__restrict__ pos_all, const T *__restrict__ charge_all,
-                                                       PmeBatch<CAP> pb, const double *__restrict__ phis,
+                                                       PB pb, const double *__restrict__ phis,
                                                        double *__restrict__ force_all,
                                                        const double *__restrict__ partials, int64_t n_part_blocks,
                                                        double *energy, double *virial) {
   __shared__ double red[kWaves][8];
-  const int atom_wgs = pb.blk0[pb.nsys];
+  const int atom_wgs = gather_wgs(pb);
   if (static_cast<int>(blockIdx.x) >= atom_wgs) {  // workgroup-uniform
     const int64_t b = pb.first + static_cast<int>(blockIdx.x) - atom_wgs;
     reduce_sym_partials(partials + b * kSymSums * n_part_blocks, n_part_blocks, 0, n_part_blocks,
@@ -703,7 +770,7 @@ __global__ void __launch_bounds__(kBlock) k_pme_gather(const T *__restrict__ pos
   // workgroup k of XCD x takes the k-th of range x of the atoms' workgroups
   const int xcd = static_cast<int>(blockIdx.x) % kXcds, nth = static_cast<int>(blockIdx.x) / kXcds;
   const int per = atom_wgs / kXcds, more = atom_wgs % kXcds;
-  const int wg = xcd * per + (xcd < more ? xcd : more) + nth;
+  const int wg = gather_wg0(pb) + xcd * per + (xcd < more ? xcd : more) + nth;
   const int sb = system_of_wg(pb, pb.blk0, wg);
   const PmeSys ps = make_sys(pb, sb);
   const T *__restrict__ pos = pos_all + 3 * pb.a0[sb];
@@ -850,6 +917,8 @@ bool pme_grid(const int K[3], int B, PmeGrid *out) {
   return true;
 }
 
+constexpr size_t kTableBytes = 2 * 24 + 8 + 3 * 4;  // of a PmeTable, per system
+
 int64_t bin_workgroups(const nb_system *sys, int b) {
   return std::max<int64_t>(sys->atom_offset[b + 1] - sys->atom_offset[b] + kBinAtoms - 1, 0) / kBinAtoms;
 }
@@ -880,6 +949,8 @@ std::string pme_layout(int B, const int32_t grid[3], PmeLayout *lay) {
   off = align256(off + sizeof(double) * static_cast<size_t>(B) * kPart * std::max<int64_t>(l.conv_blocks, l.K[2] / 2 + 1));
   l.tables = off;
   if (l.in_lds) off = align256(off + (16 + 8 + 4) * static_cast<size_t>(l.K[0] + l.K[1] + l.K[2]));
+  l.systems = off;
+  if (l.in_lds && B > kPmeChunk) off = align256(off + kTableBytes * (static_cast<size_t>(B) + 1));
   l.work = off;
   l.total = off;
   *lay = l;
@@ -902,10 +973,11 @@ std::string pme_attach_plans(PmeLayout *lay) {
 namespace {
 
 // The launch descriptor of systems [first, first + nsys).  bins: the binning workgroups of the
-// systems before them, to be carried on (null: the atoms are not binned).
+// systems before them, to be carried on (null: the atoms are not binned); before: likewise the
+// gather's (null: counted from these systems on).
 template <int CAP>
 PmeBatch<CAP> pme_chunk(const PmeLayout &lay, const nb_system *sys, double a, double ke, int first, int nsys,
-                        int32_t *bins) {
+                        int32_t *bins, int32_t *before = nullptr) {
   PmeBatch<CAP> pb;
   std::memset(&pb, 0, sizeof(pb));
   pb.nsys = nsys;
@@ -913,7 +985,7 @@ PmeBatch<CAP> pme_chunk(const PmeLayout &lay, const nb_system *sys, double a, do
   for (int d = 0; d < 3; ++d) pb.K[d] = lay.K[d];
   pb.a = a;
   pb.ke = ke;
-  int32_t blocks = 0;
+  int32_t blocks = before ? *before : 0;
   for (int k = 0; k < nsys; ++k) {
     const int b = first + k;
     for (int d = 0; d < 3; ++d) {
@@ -930,25 +1002,31 @@ PmeBatch<CAP> pme_chunk(const PmeLayout &lay, const nb_system *sys, double a, do
   }
   pb.blk0[nsys] = blocks;
   if (bins) pb.bin0[nsys] = *bins;
+  if (before) *before = blocks;
   return pb;
 }
 
-template <bool PADDED, int CAP>
-void launch_gather(const PmeBatch<CAP> &pb, const nb_system *sys, const double *phi, double *force, const double *partials,
+template <int CAP>
+int32_t gather_wgs_host(const PmeBatch<CAP> &pb) { return pb.blk0[pb.nsys]; }
+int32_t gather_wgs_host(const PmeTable &pb) { return pb.wgs; }
+
+template <bool PADDED, typename PB>
+void launch_gather(const PB &pb, const nb_system *sys, const double *phi, double *force, const double *partials,
                    int64_t n_part_blocks, double *energy, double *virial, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>(pb.blk0[pb.nsys] + ((energy || virial) ? pb.nsys : 0));
+  const unsigned grid = static_cast<unsigned>(gather_wgs_host(pb) + ((energy || virial) ? pb.nsys : 0));
   if (grid == 0) return;
   if (sys->pos_is_f64)
-    hipLaunchKernelGGL((k_pme_gather<double, PADDED, CAP>), dim3(grid), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((k_pme_gather<double, PADDED, PB>), dim3(grid), dim3(kBlock), 0, s,
                        static_cast<const double *>(sys->pos), static_cast<const double *>(sys->charge), pb, phi, force,
                        partials, n_part_blocks, energy, virial);
   else
-    hipLaunchKernelGGL((k_pme_gather<float, PADDED, CAP>), dim3(grid), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((k_pme_gather<float, PADDED, PB>), dim3(grid), dim3(kBlock), 0, s,
                        static_cast<const float *>(sys->pos), static_cast<const float *>(sys->charge), pb, phi, force,
                        partials, n_part_blocks, energy, virial);
 }
 
-// A grid transformed in LDS: five launches (per CAP systems).
+// A grid transformed in LDS: five launches.  CAP: systems that travel in one launch's arguments;
+// a larger batch bins CAP at a time, and the other launches find its systems in the table.
 template <int CAP>
 hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double beta, double ke, char *base,
                           double *force, double *energy, double *virial, hipStream_t s) {
@@ -981,43 +1059,84 @@ hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double bet
   // fill the chip, 256 (more workgroups per CU, whose phases overlap) when it does.
   const int rows_wgs = lay.K[0] * g.blocks * lay.B, slab_wgs = g.H * lay.B;
   const dim3 rows_thr(rows_wgs > 512 ? 256 : 512), slab_thr(slab_wgs > 512 ? 256 : kPlaneBlock);
-  auto each = [&](auto &&body) {
-    int32_t bins = 0;
-    for (int first = 0; first < lay.B; first += CAP)
-      body(pme_chunk<CAP>(lay, sys, a, ke, first, std::min(CAP, lay.B - first), binned ? &bins : nullptr));
-  };
-  each([&](const PmeBatch<CAP> &pb) {
-    const unsigned wgs = static_cast<unsigned>(pb.bin0[pb.nsys] - pb.bin0[0]) + (pb.first == 0 ? 3u : 0u);
-    if (wgs == 0) return;
-    if (sys->pos_is_f64)
-      hipLaunchKernelGGL((k_pme_bin<double, CAP>), dim3(wgs), dim3(kBinAtoms), 0, s, static_cast<const double *>(sys->pos),
-                         static_cast<const double *>(sys->charge), pb, g, atoms, offs);
-    else
-      hipLaunchKernelGGL((k_pme_bin<float, CAP>), dim3(wgs), dim3(kBinAtoms), 0, s, static_cast<const float *>(sys->pos),
-                         static_cast<const float *>(sys->charge), pb, g, atoms, offs);
-  });
-  each([&](const PmeBatch<CAP> &pb) {
-    const dim3 wgs(static_cast<unsigned>(lay.K[0] * g.blocks * pb.nsys));
-    auto rows = [&](const auto *from, const auto *beside) {
+  const bool f64 = sys->pos_is_f64 != 0;
+  const auto *pos64 = static_cast<const double *>(sys->pos), *q64 = static_cast<const double *>(sys->charge);
+  const auto *pos32 = static_cast<const float *>(sys->pos), *q32 = static_cast<const float *>(sys->charge);
+  // The steps after the binning, each for all of the batch before the next (phi takes the bins'
+  // place), in launches of the systems of each of parts.
+  auto steps = [&](const auto &parts) {
+    using PB = std::remove_cv_t<std::remove_reference_t<decltype(*std::begin(parts))>>;
+    auto row_wgs = [&](const PB &pb) { return dim3(static_cast<unsigned>(lay.K[0] * g.blocks * pb.nsys)); };
+    auto rows = [&](const PB &pb, const auto *from, const auto *beside) {
       using T = std::remove_const_t<std::remove_reference_t<decltype(*from)>>;
       using U = std::remove_const_t<std::remove_reference_t<decltype(*beside)>>;
-      hipLaunchKernelGGL((k_pme_rows_fwd<T, U, CAP>), wgs, rows_thr, rows_lds, s, from, beside, pb, g, spec);
+      hipLaunchKernelGGL((k_pme_rows_fwd<T, U, PB>), row_wgs(pb), rows_thr, rows_lds, s, from, beside, pb, g, spec);
     };
-    if (binned) rows(atoms, offs);
-    else if (sys->pos_is_f64) rows(static_cast<const double *>(sys->pos), static_cast<const double *>(sys->charge));
-    else rows(static_cast<const float *>(sys->pos), static_cast<const float *>(sys->charge));
-  });
-  each([&](const PmeBatch<CAP> &pb) {
-    hipLaunchKernelGGL(k_pme_slab<CAP>, dim3(static_cast<unsigned>(g.H * pb.nsys)), slab_thr, slab_lds, s, spec, pb, g,
-                       want, partials);
-  });
-  each([&](const PmeBatch<CAP> &pb) {
-    hipLaunchKernelGGL(k_pme_rows_inv<CAP>, dim3(static_cast<unsigned>(lay.K[0] * g.blocks * pb.nsys)), rows_thr, rows_lds,
-                       s, spec, pb, g, phi);
-  });
-  each([&](const PmeBatch<CAP> &pb) {
-    launch_gather<true>(pb, sys, phi, force, partials, g.H, energy, virial, s);
-  });
+    for (const PB &pb : parts) {
+      if (binned) rows(pb, atoms, offs);
+      else if (f64) rows(pb, pos64, q64);
+      else rows(pb, pos32, q32);
+    }
+    for (const PB &pb : parts)
+      hipLaunchKernelGGL(k_pme_slab<PB>, dim3(static_cast<unsigned>(g.H * pb.nsys)), slab_thr, slab_lds, s, spec, pb, g,
+                         want, partials);
+    for (const PB &pb : parts)
+      hipLaunchKernelGGL(k_pme_rows_inv<PB>, row_wgs(pb), rows_thr, rows_lds, s, spec, pb, g, phi);
+    for (const PB &pb : parts) launch_gather<true>(pb, sys, phi, force, partials, g.H, energy, virial, s);
+  };
+  int32_t bins = 0, *const binning = binned ? &bins : nullptr;
+  if (lay.B <= CAP) {
+    const PmeBatch<CAP> all[1] = {pme_chunk<CAP>(lay, sys, a, ke, 0, lay.B, binning)};
+    const PmeBatch<CAP> &pb = all[0];
+    const dim3 wgs(static_cast<unsigned>(bins) + 3u);
+    if (f64) hipLaunchKernelGGL((k_pme_bin<double, CAP>), wgs, dim3(kBinAtoms), 0, s, pos64, q64, pb, g, atoms, offs);
+    else hipLaunchKernelGGL((k_pme_bin<float, CAP>), wgs, dim3(kBinAtoms), 0, s, pos32, q32, pb, g, atoms, offs);
+    steps(all);
+    return hipGetLastError();
+  }
+  if constexpr (CAP == kPmeChunk) {
+    const size_t B = static_cast<size_t>(lay.B);
+    char *at = base + lay.systems;
+    PmeTable tab{};
+    tab.L = reinterpret_cast<double(*)[3]>(at);
+    tab.invL = tab.L + B;
+    tab.a0 = reinterpret_cast<int64_t *>(tab.invL + B);
+    tab.n = reinterpret_cast<int32_t *>(tab.a0 + B);
+    tab.blk0 = tab.n + B;
+    tab.bin0 = tab.blk0 + B + 1;
+    for (int d = 0; d < 3; ++d) tab.K[d] = lay.K[d];
+    tab.a = a;
+    tab.ke = ke;
+    // (a launch has fewer than 2^32 threads: ranges of at most 2^20 workgroups, or one system)
+    const int64_t most = std::max<int64_t>(static_cast<int64_t>(lay.K[0]) * g.blocks, g.H);
+    static_assert(kBlock / kGatherLanes == 32, "atoms per gather workgroup");
+    auto gather_wgs = [&](int b) { return (sys->atom_offset[b + 1] - sys->atom_offset[b] + 31) / 32; };
+    std::vector<PmeTable> parts;
+    for (int first = 0, end; first < lay.B; first = end) {
+      int64_t wgs = gather_wgs(first);
+      for (end = first + 1; end < lay.B; ++end) {
+        const int64_t more = gather_wgs(end);
+        if (wgs + more > (1 << 20) || (end + 1 - first) * most > (1 << 20)) break;
+        wgs += more;
+      }
+      PmeTable part = tab;
+      part.first = first;
+      part.nsys = end - first;
+      part.wgs = static_cast<int>(wgs);
+      part.L += first, part.invL += first, part.a0 += first, part.n += first, part.blk0 += first, part.bin0 += first;
+      parts.push_back(part);
+      tab.wg0 += part.wgs;
+    }
+    int32_t gathers = 0;
+    for (int first = 0; first < lay.B; first += CAP) {
+      const PmeBatch<CAP> pb = pme_chunk<CAP>(lay, sys, a, ke, first, std::min(CAP, lay.B - first), binning, &gathers);
+      const dim3 wgs(static_cast<unsigned>(pb.bin0[pb.nsys] - pb.bin0[0]) + (first == 0 ? 3u : 0u) + 1u);
+      if (f64)
+        hipLaunchKernelGGL(k_pme_bin_table<double>, wgs, dim3(kBinAtoms), 0, s, pos64, q64, pb, g, atoms, offs, tab);
+      else hipLaunchKernelGGL(k_pme_bin_table<float>, wgs, dim3(kBinAtoms), 0, s, pos32, q32, pb, g, atoms, offs, tab);
+    }
+    steps(parts);
+  }
   return hipGetLastError();
 }
 
