@@ -358,6 +358,7 @@ __global__ void __launch_bounds__(kBlock) k_pme_convolve(double2 *__restrict__ s
 constexpr int kBinAtoms = 1024;   // atoms per k_pme_bin workgroup, one per thread
 constexpr int kPhiPad = 3;        // copies of a row's last three values before it
 constexpr size_t kPmeLdsMax = 150 * 1024;  // of the 160 KB of LDS per CU
+constexpr int kCus = 256;                  // compute units of the MI355X
 
 // One atom for the charge spreading: scaled coordinates and charge.
 struct alignas(32) PmeAtom { double ux, uy, uz, q; };
@@ -904,7 +905,7 @@ bool pme_grid(const int K[3], int B, PmeGrid *out) {
   g.ys = K[1] | 1;
   // workgroups per x-plane: enough to have one on each of the 256 CUs, at most 4 (each
   // looks at all of the plane's atoms)
-  const int want = std::min<int64_t>(4, (256 + static_cast<int64_t>(K[0]) * B - 1) / (static_cast<int64_t>(K[0]) * B));
+  const int want = std::min<int64_t>(4, (kCus + static_cast<int64_t>(K[0]) * B - 1) / (static_cast<int64_t>(K[0]) * B));
   const int all = (K[1] + 1) / 2;  // row pairs of a plane
   g.pairs = (all + want - 1) / want;
   g.blocks = (all + g.pairs - 1) / g.pairs;
@@ -1056,9 +1057,15 @@ hipError_t launch_pme_lds(const PmeLayout &lay, const nb_system *sys, double bet
   const int want = (energy || virial) ? 1 : 0;
   const size_t rows_lds = rows_lds_bytes(g), slab_lds = slab_lds_bytes(g);
   // Threads per workgroup: as many as shorten one workgroup's passes while the grid does not
-  // fill the chip, 256 (more workgroups per CU, whose phases overlap) when it does.
+  // fill the chip, 256 (more workgroups per CU, whose phases overlap) when it does.  A slab of
+  // 1,024 threads has a CU to itself by its registers: from 257 on they would queue, so 512 and
+  // then 256, but for planes that have it by their LDS in any case (call, 1,024 against 512
+  // threads: 264 slabs of 20 x 20 46 and 38 us, 264 of 64 x 64 96 and 86; 276 of 90 x 90 177
+  // and 184).
   const int rows_wgs = lay.K[0] * g.blocks * lay.B, slab_wgs = g.H * lay.B;
-  const dim3 rows_thr(rows_wgs > 512 ? 256 : 512), slab_thr(slab_wgs > 512 ? 256 : kPlaneBlock);
+  const bool alone = slab_wgs <= kCus || 2 * slab_lds > kPmeLdsMax;
+  const dim3 rows_thr(rows_wgs > 2 * kCus ? 256 : 512);
+  const dim3 slab_thr(alone ? kPlaneBlock : slab_wgs > 2 * kCus ? 256 : 512);
   const bool f64 = sys->pos_is_f64 != 0;
   const auto *pos64 = static_cast<const double *>(sys->pos), *q64 = static_cast<const double *>(sys->charge);
   const auto *pos32 = static_cast<const float *>(sys->pos), *q32 = static_cast<const float *>(sys->charge);
