@@ -246,16 +246,17 @@ nb_status nb_ewald_corrections(const nb_system *sys, const nb_params *params, vo
  * precision); ewald_beta > 0 and coulomb_k come from params, which is validated as for
  * the other calls.  `workspace` is its own buffer (not the nonbonded workspace) of
  * nb_pme_workspace_bytes bytes, 256-byte aligned, owned by the caller (the size depends
- * on n_systems, the grid and the device alone); it needs no build.  It holds the grids and the work area of the FFTs, so calls with different
- * workspaces may run concurrently on different streams.  The LDS additions of the
+ * on n_systems, the grid and the device alone); it needs no build.  It holds the grids and
+ * the work area of the FFTs, so calls with different workspaces may run concurrently on
+ * different streams.  The LDS additions of the
  * charge spreading are FP64 atomics, so results may vary in the last bits from run to
  * run.  Grids whose sizes have no prime factor above 7 and whose (x, y) planes fit in LDS
  * (16 (K1 (K2 | 1) + 2 K1 + 2 K2) <= 153,600 bytes; squares up to 90 x 90) are transformed
  * by the library's own kernels.  Other grids use hipFFT plans (each transforming every
- * system of the batch in one call) made on the first use of a grid shape and batch size on a device, by
- * nb_pme_workspace_bytes (which therefore needs a current HIP device) or
- * nb_pme_reciprocal, and kept until the process ends (only their read-only tables:
- * they allocate no work buffers of their own); at most 32 such plans per process.
+ * system of the batch in one call) made on the first use of a grid shape and batch size on
+ * a device, by nb_pme_workspace_bytes (which therefore needs a current HIP device) or
+ * nb_pme_reciprocal, and kept until the process ends (only their read-only tables: they
+ * allocate no work buffers of their own); at most 32 such plans per process.
  * Returns NB_ERR_HIP if the FFT library refuses a plan or a transform or the 32 are
  * used up. */
 nb_status nb_pme_workspace_bytes(const nb_system *sys, const int32_t grid[3] /*[host]*/, size_t *bytes /*[host]*/);

@@ -44,12 +44,13 @@ void set_error(const std::string &msg) { g_last_error = msg; }
 // waves to hide its latency.  As many parts as keep every wave resident (about 4,000 waves;
 // 3,000 for the FP64 force VJP, whose LDS is larger), at most kMaxParts (each has its own sums in
 // the workspace, which eight would more than double for a small system); on the FP64 path three up to
-// 4,096 clusters, whose long waves then end more evenly.  Measured, call time with 1 part
-// against this rule (us): mixed adjoint 648 atoms 26 -> 16, 7.6k 37 -> 28, 13.7k 46 -> 42 and
-// 23.6k 60 -> 63 with 2 (kept whole); FP64 adjoint 50 -> 24, 70 -> 45, 90 -> 72, 116 -> 104;
-// FP64 force VJP 58 -> 27, 81 -> 59, 105 -> 95, 159 -> 142, and 48.6k atoms 243 -> 252 with 3
-// (kept whole).  (Forces and energies stay whole: the same system gives the same bits alone
-// and in a batch of any size.)
+// 4,096 clusters, whose long waves then end more evenly.  Measured on boxes of water, call time
+// with 1 part against this rule (us): mixed adjoint 648 atoms 26 -> 16, 7.6k 38 -> 28, 13.7k
+// 44 -> 41 and 23.6k 52 -> 59 with 2 (kept whole); FP64 adjoint 50 -> 23, 72 -> 45, 86 -> 69,
+// 101 -> 99; FP64 force VJP 58 -> 27, 83 -> 60, 99 -> 92, 149 -> 135.  Above, with items split
+// in two: 35k atoms FP64 adjoint 148 -> 137 and VJP 195 -> 186 (not taken), 48.6k 176 -> 176
+// and 241 -> 241, 70k 228 -> 241 and 318 -> 331.  (Forces and energies stay whole: the same
+// system gives the same bits alone and in a batch of any size.)
 constexpr int kMaxParts = 4;
 constexpr int64_t kPartsClusters = 4096;  // the most clusters that are cut, into three
 int grad_parts_for(const Plan &p, int mode) {

@@ -284,7 +284,8 @@ __device__ inline void fold_row(const Dev &d, uint4 *masks, const int32_t *__res
   if (own3) atomicOr(&w[3], own3);
 }
 
-// The pair lists of one build, folded by workgroups of the scatter's launch.
+// The pair lists of one build, folded by workgroups beside the scan (k_scan_scatter's or
+// k_scan_apply's).
 struct PairLists {
   const int32_t *excl_off, *excl_idx, *p14_off, *p14_idx;
 };

@@ -28,8 +28,8 @@
 // 23.6k-atom box, a chain of dependent loads and one erf per partner): the partners'
 // loads are issued together, and sums that nobody asked for are not formed.  With the
 // far pass and the reduction in launches of their own and ten sums reduced one by one the
-// call took 17.9 us there; now 15.0, of which the GPU works 9 (5.6 + 3.1 traced, against
-// 8.6 + 2.5 + 4.0).
+// GPU worked 15 us there (8.6 + 2.5 + 4.0 traced); now 9 (5.6 + 3.1), and the call, bound by
+// the host, takes 10.3.
 #include "nb_internal.h"
 #include "nb_ewald.h"
 #include "nb_pair_common.h"

@@ -222,24 +222,6 @@ __device__ __forceinline__ void to_fixed2(double v, long long &hi, long long &lo
   hi = static_cast<long long>((static_cast<unsigned long long>(static_cast<long long>(static_cast<int>(h))) << 32) +
                               static_cast<unsigned long long>(static_cast<unsigned>(l)));
 }
-// Index of the last column whose first cluster is <= k: a 64-way search, each lane
-// probing one position per round (two or three rounds for any practical grid).
-__device__ __forceinline__ int cluster_column(const int32_t *__restrict__ col_clu_start, int n_columns, int k) {
-  int lo = 0, hi = n_columns - 1;  // answer in [lo, hi]
-  const int lane = threadIdx.x & 63;
-  while (hi > lo) {
-    const int span = hi - lo + 1;
-    const int step = (span + 63) >> 6;
-    const int probe = lo + lane * step;
-    const bool le = probe <= hi && col_clu_start[probe] <= k;
-    const uint64_t m = __ballot(le);
-    const int last = 63 - __clzll(static_cast<long long>(m));  // lane 0 always passes
-    lo = lo + last * step;
-    const int nhi = lo + step - 1;
-    hi = nhi < hi ? nhi : hi;
-  }
-  return lo;
-}
 
 // EXW: the rows' exclusion windows are held in LDS, as bytes.
 template <bool F64, bool EXW>

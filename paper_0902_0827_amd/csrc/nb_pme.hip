@@ -25,11 +25,11 @@
 //   k_pme_slab     one workgroup per (system, z frequency): the FFTs along y and x in LDS,
 //                  C(m) with the energy and virial terms, and the inverse FFTs;
 //   k_pme_rows_inv per (system, x, block of y rows): the inverse FFT along z, giving phi;
-//   k_pme_gather   4 lanes per atom: its force from phi and the spline derivatives; its
+//   k_pme_gather   8 lanes per atom: its force from phi and the spline derivatives; its
 //                  last workgroups sum each system's energy and virial partials in order.
 //
 // Between the kernels the spectrum crosses memory twice instead of eight times, and nine
-// launches are five.  Measured with energy and virial, MI355X: 63.3 -> 47.2 us per call for
+// launches are five.  Measured with energy and virial, MI355X: 63.2 -> 45.0 us per call for
 // 23.6k atoms at 64^3, 224 -> 109 us for 24 systems (293k atoms) at 48^3.  (x-planes
 // transformed whole, with a third kernel for the x lines, took 69 and 255 us: one system
 // then has 64 workgroups, all of whose LDS additions queue on 64 CUs.)

@@ -25,18 +25,7 @@ struct FftShape {
   int n = 0, passes = 0;
   int radix[kFftMaxPasses] = {};
 
-  // Position of frequency f after the forward transform.
-  __device__ int pos(int f) const {
-    int at = 0, s = n;
-    for (int k = 0; k < passes; ++k) {
-      const int r = radix[k], q = f / r;
-      s /= r;
-      at += (f - q * r) * s;
-      f = q;
-    }
-    return at;
-  }
-  // Frequency at position p (the inverse of pos).
+  // Frequency at position p after the forward transform.
   __device__ int freq(int p) const {
     int f = 0, w = 1, s = n;
     for (int k = 0; k < passes; ++k) {
